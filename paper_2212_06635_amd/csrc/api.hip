@@ -143,7 +143,7 @@ static void *scratch_address(tmx_ctx *c)
 static size_t red_partials_bytes(const tmx_ctx *c) { return sizeof(double) * c->red.max_blocks * MAXR * 4; }
 static size_t red_result_bytes() { return sizeof(double) * MAXR * 4; }
 
-static size_t bytes_per_real(int prec) { return prec == F64 ? 8 : (prec == F32 ? 4 : 2); }
+static size_t bytes_per_real(int prec) { return prec == F64 ? 8 : (prec == F32 ? 4 : 2); }  // F16, F16A: 2
 
 double mhat_bytes_per_site(int prec, int nf, int nrhs)
 {
@@ -166,7 +166,8 @@ int fetch(tmx_ctx *c, int n, double *host)
 // ---------------------------------------------------------------------------
 // derived fields
 // ---------------------------------------------------------------------------
-static size_t clover_bytes(int prec, long Vh) { return 144 * bytes_per_real(prec) * Vh; }  // both parities
+// both parities: 56 reals a site structured, 72 general
+static size_t clover_bytes(int prec, long Vh, bool ct) { return (ct ? 112 : 144) * bytes_per_real(prec) * Vh; }
 static size_t inv_bytes(int prec, long Vh) { return 144 * bytes_per_real(prec) * Vh; }     // even sites
 static size_t invnd_bytes(int prec, long Vh) { return 72 * bytes_per_real(prec) * Vh; }    // even sites
 static size_t link_bytes(int prec, long Vh)
@@ -189,38 +190,64 @@ static int ensure_links(tmx_ctx *c, int prec)
     return TMX_OK;
 }
 
-static int ensure_clover(tmx_ctx *c, int prec)
+// the clover buffer of a slot, large enough for either format: a clover term
+// given by the caller after one built from the links (or the other way round)
+// needs no new buffer
+static int clover_buffer(tmx_ctx *c, int slot)
+{
+    if (!c->clov[slot]) c->clov[slot] = dev_alloc(c, clover_bytes(slot, c->Vh, false));
+    return c->clov[slot] ? TMX_OK : set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
+}
+
+// the block slot an apply reads, and whether it holds structured blocks
+// (clover terms built from the links) or general ones (F16A, and every slot
+// of a clover term given by the caller)
+static int clover_slot(const tmx_ctx *c, int prec, bool inner)
+{
+    return prec == F16 && !inner && !c->clover_from_host ? F16A : prec;
+}
+static bool clover_ct(const tmx_ctx *c, int slot) { return !c->clover_from_host && slot != F16A; }
+
+static int ensure_clover(tmx_ctx *c, int slot)
 {
     if (!c->gauge_loaded) return set_err(c, TMX_ENOTLOADED, "no gauge field loaded");
     if (!c->have_params) return set_err(c, TMX_ENOTLOADED, "parameters not set");
     if (!c->clov_ok[F64]) {
-        if (!c->clov[F64]) {
-            c->clov[F64] = dev_alloc(c, clover_bytes(F64, c->Vh));
-            if (!c->clov[F64]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
-        int r = hip_err(c, launch_clover_build((const double *)c->links[F64], (double *)c->clov[F64], c->g,
-                                               c->par.kappa, c->par.csw, c->stream),
-                        "clover build");
+        int r = clover_buffer(c, F64);
+        if (r) return r;
+        double *cl = static_cast<double *>(c->clov[F64]);
+        r = hip_err(c, launch_clover_build((const double *)c->links[F64], cl, c->g, c->par.kappa, c->par.csw, c->stream),
+                    "clover build");
+        if (!r) r = hip_err(c, launch_clover_check(cl, c->g, c->stream), "clover check");
         if (r) return r;
         c->clov_ok[F64] = true;
         c->clov_kappa = c->par.kappa;
         c->clov_csw = c->par.csw;
-        c->clov_ok[F32] = c->clov_ok[F16] = false;
+        c->clov_ok[F32] = c->clov_ok[F16] = c->clov_ok[F16A] = false;
         c->inv_ok[0] = c->inv_ok[1] = c->inv_ok[2] = false;
         c->invnd_ok[0] = c->invnd_ok[1] = c->invnd_ok[2] = false;
     }
-    if (prec != F64 && !c->clov_ok[prec]) {
-        if (!c->clov[prec]) {
-            c->clov[prec] = dev_alloc(c, clover_bytes(prec, c->Vh));
-            if (!c->clov[prec]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
-        int r = hip_err(c, launch_convert_seq((const double *)c->clov[F64], c->clov[prec], prec, 144, c->Vh, c->stream),
-                        "convert clover");
+    if (slot != F64 && !c->clov_ok[slot]) {
+        const bool ct = clover_ct(c, slot);
+        int r = clover_buffer(c, slot);
         if (r) return r;
-        c->clov_ok[prec] = true;
+        const double *src = static_cast<const double *>(c->clov[F64]);
+        r = hip_err(c, ct             ? launch_convert_ct(src, c->clov[slot], slot, c->Vh, c->stream)
+                       : slot == F16A ? launch_convert_ct_general16(src, c->clov[slot], c->Vh, c->stream)
+                                      : launch_convert_seq(src, c->clov[slot], slot, 144, c->Vh, c->stream),
+                    "convert clover");
+        if (r) return r;
+        c->clov_ok[slot] = true;
     }
     return TMX_OK;
 }
+
+// The site blocks of K1 are inverted in the kernel where they are structured
+// and each serves one slot: one right-hand side of one flavour.  With several
+// right-hand sides the threads of a site share the stored inverse's cache
+// lines (144 / nrhs reals a slot), and repeating the elimination of some 900
+// multiply-adds for each of them would cost more than the bytes it saves.
+static bool can_solve(const tmx_ctx *c, int slot, bool nd) { return !nd && clover_ct(c, slot); }
 
 static int ensure_inv(tmx_ctx *c, int prec)
 {
@@ -233,7 +260,7 @@ static int ensure_inv(tmx_ctx *c, int prec)
             c->inv[F64] = dev_alloc(c, inv_bytes(F64, c->Vh));
             if (!c->inv[F64]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
         }
-        r = hip_err(c, launch_clover_inv((const double *)c->clov[F64], (double *)c->inv[F64], c->g, nu, c->stream),
+        r = hip_err(c, launch_clover_inv((const double *)c->clov[F64], clover_ct(c, F64), (double *)c->inv[F64], c->g, nu, c->stream),
                     "clover inverse");
         if (r) return r;
         c->inv_ok[F64] = true;
@@ -265,8 +292,8 @@ static int ensure_invnd(tmx_ctx *c, int prec)
             c->invnd[F64] = dev_alloc(c, invnd_bytes(F64, c->Vh));
             if (!c->invnd[F64]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
         }
-        r = hip_err(c, launch_clover_inv_nd((const double *)c->clov[F64], (double *)c->invnd[F64], c->g, nb, ep,
-                                            c->stream),
+        r = hip_err(c, launch_clover_inv_nd((const double *)c->clov[F64], clover_ct(c, F64), (double *)c->invnd[F64],
+                                            c->g, nb, ep, c->stream),
                     "nd clover inverse");
         if (r) return r;
         c->invnd_ok[F64] = true;
@@ -286,21 +313,41 @@ static int ensure_invnd(tmx_ctx *c, int prec)
     return TMX_OK;
 }
 
-int ensure_ready(tmx_ctx *c, int prec, bool nd)
+int ensure_ready(tmx_ctx *c, int prec, bool nd, int nrhs, bool inner)
 {
     if (prec < F64 || prec > F16) return set_err(c, TMX_EINVAL, "bad precision");
+    const int slot = clover_slot(c, prec, inner);
     int r = ensure_links(c, prec);
-    if (!r) r = ensure_clover(c, prec);
-    if (!r) r = nd ? ensure_invnd(c, prec) : ensure_inv(c, prec);
-    return r;
+    if (!r) r = ensure_clover(c, slot);
+    if (r || (nrhs == 1 && can_solve(c, slot, nd))) return r;
+    return nd ? ensure_invnd(c, prec) : ensure_inv(c, prec);
 }
 
 // ---------------------------------------------------------------------------
 // operator layer
 // ---------------------------------------------------------------------------
-static const void *clov_parity(tmx_ctx *c, int prec, int parity)
+static const void *clov_parity(tmx_ctx *c, int slot, int parity)
 {
-    return static_cast<const char *>(c->clov[prec]) + (size_t)parity * 72 * bytes_per_real(prec) * c->Vh;
+    return static_cast<const char *>(c->clov[slot]) + parity * clover_bytes(slot, c->Vh, clover_ct(c, slot)) / 2;
+}
+
+// site data of a K1 launch and its mode: the stored inverse if it is there and
+// up to date (ensure_ready builds it where it is the faster one), else A itself
+static int k1_blocks(tmx_ctx *c, DslashArgs &a, int prec, bool nd, int nrhs, bool inner)
+{
+    const int slot = clover_slot(c, prec, inner);
+    a.clov = clov_parity(c, slot, 0);
+    a.ct = clover_ct(c, slot);
+    a.inv = nd ? c->invnd[prec] : c->inv[prec];
+    const bool stored = nd ? c->invnd_ok[prec] : c->inv_ok[prec];
+    return can_solve(c, slot, nd) && (nrhs == 1 || !stored) ? MODE_SOLVE : MODE_INV;
+}
+
+static void k2_blocks(tmx_ctx *c, DslashArgs &b, int prec, bool inner, int parity = 1)
+{
+    const int slot = clover_slot(c, prec, inner);
+    b.clov = clov_parity(c, slot, parity);
+    b.ct = clover_ct(c, slot);
 }
 
 LaunchCfg launch_cfg(tmx_ctx *c, const std::string &key)
@@ -387,7 +434,7 @@ static DslashArgs base_args(tmx_ctx *c, int prec, bool nd, int nrhs)
 // K2 on each group of rg right-hand sides, so that a group's neighbour
 // spinors stay in L2 between the two halves)
 static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int prec, bool nd, int nrhs, int sgn,
-                      int g5in, int g5out, double *nrm = nullptr, double rho = 0.0)
+                      int g5in, int g5out, double *nrm = nullptr, double rho = 0.0, bool inner = false)
 {
     const int nf = nd ? 2 : 1;
     const std::string k1 = kname("K1", prec, nd, nrhs), k2 = kname("K2", prec, nd, nrhs);
@@ -398,8 +445,7 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
     a.parity = 0;
     a.out = u;
     a.in = in;
-    a.clov = clov_parity(c, prec, 0);
-    a.inv = nd ? c->invnd[prec] : c->inv[prec];
+    const int k1mode = k1_blocks(c, a, prec, nd, nrhs, inner);
     a.g5in = g5in;
     a.xcd = l1.xcd;
     a.spt = l1.spt;
@@ -409,7 +455,7 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
     b.out = out;
     b.in = u;
     b.x = in;
-    b.clov = clov_parity(c, prec, 1);
+    k2_blocks(c, b, prec, inner);
     b.kfac = c->par.kappa * c->par.kappa;
     b.g5x = g5in;
     b.g5out = g5out;
@@ -421,11 +467,11 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
         a.r0 = b.r0 = r0;
         a.rg = b.rg = rg;
         kstat_begin(c, k1);
-        hipError_t e = launch_dslash(prec, nf, 0, a, c->stream, l1.block);
+        hipError_t e = launch_dslash(prec, nf, k1mode, a, c->stream, l1.block);
         kstat_end(c);
         if (e != hipSuccess) return hip_err(c, e, "K1 launch");
         kstat_begin(c, k2);
-        e = launch_dslash(prec, nf, 1, b, c->stream, l2.block);
+        e = launch_dslash(prec, nf, MODE_DIAG, b, c->stream, l2.block);
         kstat_end(c);
         if (e != hipSuccess) return hip_err(c, e, "K2 launch");
     }
@@ -465,7 +511,7 @@ int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagge
     int r = check_op(c, op);
     if (r) return r;
     const bool nd = op == TMX_OP_ND;
-    r = ensure_ready(c, prec, nd);
+    r = ensure_ready(c, prec, nd, nrhs);
     if (r) return r;
     const int nf = nd ? 2 : 1;
     const long stride = c->Vh * nrhs;
@@ -474,12 +520,12 @@ int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagge
     return mhat_with(c, out, in, make_spinor(ud, prec, nf, stride), op, prec, dagger, nrhs);
 }
 
-int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, double *nrm)
+int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, double *nrm, bool inner)
 {
     int r = check_op(c, op);
     if (r) return r;
     const bool nd = op == TMX_OP_ND;
-    r = ensure_ready(c, prec, nd);
+    r = ensure_ready(c, prec, nd, nrhs, inner);
     if (r) return r;
     const int nf = nd ? 2 : 1;
     const long stride = c->Vh * nrhs;
@@ -492,9 +538,9 @@ int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs
     // adjoint of Mhat(sgn)), so <in, N in> = |v|^2 per slot if nrm is given.
     // For What: v = What^sgn in, out = What^-sgn v = (What^sgn)^dagger What^sgn in.
     const bool w = op_is_w(op);
-    r = schur_pair(c, v, in, u, prec, nd, nrhs, sgn, 0, 1, nrm, w ? w_rho(c, sgn) : 0.0);
+    r = schur_pair(c, v, in, u, prec, nd, nrhs, sgn, 0, 1, nrm, w ? w_rho(c, sgn) : 0.0, inner);
     if (r) return r;
-    return schur_pair(c, out, v, u, prec, nd, nrhs, -sgn, 0, 1, nullptr, w ? w_rho(c, -sgn) : 0.0);
+    return schur_pair(c, out, v, u, prec, nd, nrhs, -sgn, 0, 1, nullptr, w ? w_rho(c, -sgn) : 0.0, inner);
 }
 
 int op_D(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec)
@@ -504,7 +550,7 @@ int op_D(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec)
     if (op_is_w(op)) return set_err(c, TMX_EINVAL, "What^pm is defined for the Schur operator only");
     const bool nd = op == TMX_OP_ND;
     r = ensure_links(c, prec);
-    if (!r) r = ensure_clover(c, prec);
+    if (!r) r = ensure_clover(c, clover_slot(c, prec, false));
     if (r) return r;
     const int nf = nd ? 2 : 1;
     const int sgn = nd ? 1 : op;
@@ -515,11 +561,11 @@ int op_D(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec)
         a.out = parity_half(out, prec, nf, p);
         a.in = parity_half(in, prec, nf, 1 - p);
         a.x = parity_half(in, prec, nf, p);
-        a.clov = clov_parity(c, prec, p);
+        k2_blocks(c, a, prec, false, p);
         a.kfac = c->par.kappa;
         const LaunchCfg l = launch_cfg(c, kname("K2", prec, nd, 1));
         a.xcd = l.xcd;
-        hipError_t e = launch_dslash(prec, nf, 1, a, c->stream, l.block);
+        hipError_t e = launch_dslash(prec, nf, MODE_DIAG, a, c->stream, l.block);
         if (e != hipSuccess) return hip_err(c, e, "D launch");
     }
     return TMX_OK;
@@ -606,7 +652,7 @@ static int tune_pick(tmx_ctx *c, const DslashArgs &a, int prec, int nf, int mode
         if (r) return r;
         if (log)
             std::fprintf(stderr, "# TMX: tune %s prec %d nf %d nrhs %d block %d xcd %d spt %d rg %d: %.4f ms\n",
-                         mode ? "K2" : "K1", prec, nf, a.nrhs, l.block, l.xcd, l.spt, l.rg, ms);
+                         mode == MODE_DIAG ? "K2" : "K1", prec, nf, a.nrhs, l.block, l.xcd, l.spt, l.rg, ms);
         if (ms < *best_ms) {
             *best_ms = ms;
             *best = l;
@@ -698,6 +744,7 @@ int tmx_destroy(tmx_ctx *c)
 {
     if (!c) return TMX_EINVAL;
     (void)hipStreamSynchronize(c->stream);
+    dev_free(c, c->clov[F16A]);
     for (int p = 0; p < 3; ++p) {
         dev_free(c, c->links[p]);
         dev_free(c, c->clov[p]);
@@ -841,12 +888,9 @@ int tmx_load_clover(tmx_ctx *c, const double *host_T)
     const size_t bytes = (size_t)c->V * 144 * 8;
     void *stage = dev_alloc(c, bytes);
     if (!stage) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-    if (!c->clov[F64]) {
-        c->clov[F64] = dev_alloc(c, clover_bytes(F64, c->Vh));
-        if (!c->clov[F64]) {
-            dev_free(c, stage);
-            return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
+    if (clover_buffer(c, F64)) {
+        dev_free(c, stage);
+        return TMX_ENOMEM;
     }
     hipError_t e = hipMemcpyAsync(stage, host_T, bytes, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = launch_clover_from_canonical((const double *)stage, (double *)c->clov[F64], c->g, c->stream);
@@ -868,7 +912,7 @@ int tmx_get_clover(tmx_ctx *c, double *host_T)
     const size_t bytes = (size_t)c->V * 144 * 8;
     void *stage = dev_alloc(c, bytes);
     if (!stage) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-    hipError_t e = launch_clover_to_canonical((const double *)c->clov[F64], (double *)stage, c->g, c->stream);
+    hipError_t e = launch_clover_to_canonical((const double *)c->clov[F64], clover_ct(c, F64), (double *)stage, c->g, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(host_T, stage, bytes, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     dev_free(c, stage);
@@ -936,12 +980,14 @@ int tmx_apply_mhat_noalloc(tmx_ctx *c, void *out, const void *in, int op, int pr
                                           "-byte scratch (use tmx_apply_mhat)");
     // every derived field of this precision must exist already (building one
     // would allocate); rebuilding an existing one after new parameters does not
-    const bool have = c->gauge_loaded && c->have_params && c->links[prec] && c->clov[F64] && c->clov[prec] &&
-                      (nd ? (c->invnd[F64] && c->invnd[prec]) : (c->inv[F64] && c->inv[prec]));
-    if (!have)
+    const int slot = clover_slot(c, prec, false);
+    const bool have = c->gauge_loaded && c->have_params && c->links[prec] && c->clov[F64] && c->clov[slot];
+    const bool inv = nd ? (c->invnd[F64] && c->invnd[prec]) : (c->inv[F64] && c->inv[prec]);
+    if (!have || (!inv && !can_solve(c, slot, nd)))
         return set_err(c, TMX_ENOTLOADED, "tmx_apply_mhat_noalloc: the fields of this precision are not resident "
                                           "(one tmx_apply_mhat in this precision and sector builds them)");
-    r = ensure_ready(c, prec, nd);
+    // without a resident inverse the blocks are inverted in the kernel for any nrhs
+    r = ensure_ready(c, prec, nd, inv ? nrhs : 1);
     if (r) return r;
     void *u = scratch_address(c);
     if (!u) return TMX_EHIP;
@@ -997,19 +1043,18 @@ static int force_fields_internal(tmx_ctx *c, SpinorPtr X, SpinorPtr Y, int op, F
     const LaunchCfg l1 = launch_cfg(c, kname("K1", F64, nd, 1));
     DslashArgs a = base_args(c, F64, nd, 1);
     a.parity = 0;
-    a.clov = clov_parity(c, F64, 0);
-    a.inv = nd ? c->invnd[F64] : c->inv[F64];
+    const int k1mode = k1_blocks(c, a, F64, nd, 1, false);
     a.xcd = l1.xcd;
     a.sgn = sgn;
     a.in = ff.X;
     a.out = ff.u;
-    hipError_t e = launch_dslash(F64, nf, 0, a, c->stream, l1.block);
+    hipError_t e = launch_dslash(F64, nf, k1mode, a, c->stream, l1.block);
     if (e != hipSuccess) return hip_err(c, e, "K1 launch");
     a.sgn = -sgn;
     a.g5in = 1;
     a.in = ff.Y;
     a.out = ff.w;
-    e = launch_dslash(F64, nf, 0, a, c->stream, l1.block);
+    e = launch_dslash(F64, nf, k1mode, a, c->stream, l1.block);
     return e != hipSuccess ? hip_err(c, e, "K1 launch") : TMX_OK;
 }
 
@@ -1135,7 +1180,7 @@ int tmx_tune(tmx_ctx *c, int prec, int op, int nrhs)
     if (!c || prec < 0 || prec > 2 || nrhs < 1 || nrhs > MAXR) return c ? set_err(c, TMX_EINVAL, "tmx_tune: bad argument") : TMX_EINVAL;
     if (op != TMX_OP_PLUS && op != TMX_OP_MINUS && op != TMX_OP_ND) return set_err(c, TMX_EINVAL, "bad op");
     const bool nd = op == TMX_OP_ND;
-    int r = ensure_ready(c, prec, nd);
+    int r = ensure_ready(c, prec, nd, nrhs);
     if (r) return r;
     const int nf = nd ? 2 : 1;
     const long stride = c->Vh * nrhs;
@@ -1151,15 +1196,14 @@ int tmx_tune(tmx_ctx *c, int prec, int op, int nrhs)
     a.parity = 0;
     a.out = u;
     a.in = in;
-    a.clov = clov_parity(c, prec, 0);
-    a.inv = nd ? c->invnd[prec] : c->inv[prec];
+    const int k1mode = k1_blocks(c, a, prec, nd, nrhs, false);
     DslashArgs b = base_args(c, prec, nd, nrhs);
     b.sgn = a.sgn;
     b.parity = 1;
     b.out = out;
     b.in = u;
     b.x = in;
-    b.clov = clov_parity(c, prec, 1);
+    k2_blocks(c, b, prec, false);
     b.kfac = c->par.kappa * c->par.kappa;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return hip_err(c, hipGetLastError(), "tune events");
@@ -1182,8 +1226,8 @@ int tmx_tune(tmx_ctx *c, int prec, int op, int nrhs)
                 for (int spt = 1; spt <= (nrhs == 1 ? 2 : 1); ++spt) cands.push_back(LaunchCfg{blk, xcd, spt, g});
         LaunchCfg c1, c2;
         double t1, t2;
-        r = tune_pick(c, a, prec, nf, 0, cands, e0, e1, &c1, &t1);
-        if (!r) r = tune_pick(c, b, prec, nf, 1, cands, e0, e1, &c2, &t2);
+        r = tune_pick(c, a, prec, nf, k1mode, cands, e0, e1, &c1, &t1);
+        if (!r) r = tune_pick(c, b, prec, nf, MODE_DIAG, cands, e0, e1, &c2, &t2);
         if (r) break;
         if (t1 + t2 < best_ms) {
             best_ms = t1 + t2;

@@ -11,6 +11,13 @@
 //     two flavours: (A + X)^{-1} = (A - X) (A^2 + nubar^2 - epst^2)^{-1},
 //     X = i sgn nubar g5 tau3 - epst tau1, with A and the Hermitian inverse
 //     factor stored.
+//   MODE_SOLVE (K1 with the site block inverted in the kernel, one flavour):
+//       out = B_p^{-1}(sgn) (H in)(s) by elimination on the stored A itself.
+//       The stencils are bound by HBM bytes (a wave spends some 130k cycles
+//       mostly waiting, against about 4k for the two eliminations), so 56
+//       reals of site data instead of the inverse's 144 is what counts: with
+//       the structured A in K2 (56 instead of 72) the FP64 Mhat at 32^3x64
+//       went from 772 to 633 us, the FP16 MP-CG from 66.1 to 58.9 ms.
 //   MODE_DIAG (second half, "K2", or one parity of the full operator D):
 //       out = (A_p + X(sgn)) x(s) - kfac (H in)(s)
 //     with X = i sgn nu g5 (degenerate) or the two-flavour X above; for the
@@ -32,7 +39,7 @@
 
 namespace tmx {
 
-enum { MODE_INV = 0, MODE_DIAG = 1 };
+
 
 // acc += (1 + sgn gamma_mu) * bc * W psi,  W = U (fwd) or U^dagger (bwd)
 template <int MU, int SGN, bool DAG, typename R>
@@ -178,14 +185,14 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int
     }
 }
 
-template <int P, int NF, int MODE>
+template <int P, int NF, int MODE, bool CT>
 __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs);
 
 // Thread i takes the work items i, i + G, ..., i + (SPT - 1) G (G the grid's
 // thread count); item u is right-hand side r0 + u % rg of site u / rg.  SPT
 // is a template parameter: a runtime loop costs registers (and occupancy)
 // even when it runs once.
-template <int P, int NF, int MODE, int SPT>
+template <int P, int NF, int MODE, int SPT, bool CT>
 __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
 {
     const long rg = a.rg;
@@ -194,18 +201,34 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
     if constexpr (SPT == 1) {
         if (u >= n) return;
         const int s = (int)(u / rg);
-        dslash_slot<P, NF, MODE>(a, s, a.r0 + (u - (long)s * rg));
+        dslash_slot<P, NF, MODE, CT>(a, s, a.r0 + (u - (long)s * rg));
     } else {
         const long G = (long)gridDim.x * blockDim.x;
         for (int k = 0; k < SPT && u < n; ++k, u += G) {
             const int s = (int)(u / rg);
-            dslash_slot<P, NF, MODE>(a, s, a.r0 + (u - (long)s * rg));
+            dslash_slot<P, NF, MODE, CT>(a, s, a.r0 + (u - (long)s * rg));
         }
     }
 }
 
+// (A_chir + i tw) v for both flavours (structured or general blocks)
+template <int P, bool CT, typename R>
+__device__ __forceinline__ void apply_clov(const void *clov, long cs, long s, int c, R tw0, const cx<R> *v0, cx<R> *o0,
+                                           R tw1, const cx<R> *v1, cx<R> *o1)
+{
+    if constexpr (CT) {
+        R b[28];
+        load_ct<P>(clov, cs, s, c, b);
+        ct_apply(b, tw0, v0, o0);
+        ct_apply(b, tw1, v1, o1);
+    } else {
+        herm_apply_c<P>(clov, cs, s, c, tw0, v0, o0);
+        herm_apply_c<P>(clov, cs, s, c, tw1, v1, o1);
+    }
+}
+
 // one output slot: site s (of the output parity), right-hand side rhs
-template <int P, int NF, int MODE>
+template <int P, int NF, int MODE, bool CT>
 __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs)
 {
     using R = typename RealOf<P>::type;
@@ -233,7 +256,19 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
     // site-block epilogue, one chirality block at a time (register fences
     // keep the two blocks' matrices from being live together)
     cx<R> out[NF][12];
-    if constexpr (MODE == MODE_INV) {
+    if constexpr (MODE == MODE_SOLVE) {
+        static_assert(CT && NF == 1, "the in-kernel solve takes structured blocks of one flavour");
+        const R nb = R(a.sgn * a.nu);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            R b[28];
+            load_ct<P>(a.clov, cs, s, c, b);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) out[0][6 * c + k] = acc[0][6 * c + k];
+            ct_solve(b, c == 0 ? nb : -nb, out[0] + 6 * c);
+            reg_fence(out[0] + 6 * c, 6);
+        }
+    } else if constexpr (MODE == MODE_INV) {
         if constexpr (NF == 1) {
             const bool dag = a.sgn < 0;
             full_apply<P>(a.inv, cs, s, 0, dag, acc[0], out[0]);
@@ -250,8 +285,7 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                 herm_apply_c<P>(a.inv, cs, s, c, R(0), acc[1] + 6 * c, t1);
                 reg_fence(t0, 6);
                 reg_fence(t1, 6);
-                herm_apply_c<P>(a.clov, cs, s, c, -tw, t0, out[0] + 6 * c);
-                herm_apply_c<P>(a.clov, cs, s, c, tw, t1, out[1] + 6 * c);
+                apply_clov<P, CT>(a.clov, cs, s, c, -tw, t0, out[0] + 6 * c, tw, t1, out[1] + 6 * c);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
                     out[0][6 * c + k] = out[0][6 * c + k] + ep * t1[k];
@@ -274,7 +308,13 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                 load_chiral<P>(a.x, 0, t, c, xv);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) xv[k] = gx * xv[k];
-                herm_apply_c<P>(a.clov, cs, s, c, tw, xv, out[0] + 6 * c);
+                if constexpr (CT) {
+                    R b[28];
+                    load_ct<P>(a.clov, cs, s, c, b);
+                    ct_apply(b, tw, xv, out[0] + 6 * c);
+                } else {
+                    herm_apply_c<P>(a.clov, cs, s, c, tw, xv, out[0] + 6 * c);
+                }
                 if (a.rho != 0.0) {
                     // + i rho x on the final output: before the output gamma5,
                     // the lower chirality takes the opposite sign
@@ -292,8 +332,7 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                     x0[k] = gx * x0[k];
                     x1[k] = gx * x1[k];
                 }
-                herm_apply_c<P>(a.clov, cs, s, c, tw, x0, out[0] + 6 * c);
-                herm_apply_c<P>(a.clov, cs, s, c, -tw, x1, out[1] + 6 * c);
+                apply_clov<P, CT>(a.clov, cs, s, c, tw, x0, out[0] + 6 * c, -tw, x1, out[1] + 6 * c);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
                     out[0][6 * c + k] = out[0][6 * c + k] - ep * x1[k];
@@ -329,7 +368,7 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
     for (int f = 0; f < NF; ++f) store_spinor<P, P != F16>(a.out, f, t, out[f]);
 }
 
-template <int P, int NF, int MODE>
+template <int P, int NF, int MODE, bool CT>
 static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
 {
     const long n = (long)a.g.Vh * (a.rg > 0 ? a.rg : a.nrhs);
@@ -337,10 +376,29 @@ static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
     const int grid = (int)((n + per - 1) / per);
     if (n == 0) return hipSuccess;
     if (a.spt == 2)
-        hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 2>), dim3(grid), dim3(block), 0, st, a);
+        hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 2, CT>), dim3(grid), dim3(block), 0, st, a);
     else
-        hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 1>), dim3(grid), dim3(block), 0, st, a);
+        hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 1, CT>), dim3(grid), dim3(block), 0, st, a);
     return hipGetLastError();
+}
+
+template <int P, int NF>
+static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int block)
+{
+    if (mode == MODE_SOLVE) {
+        if constexpr (NF == 1)
+            return a.ct ? launch_one<P, NF, MODE_SOLVE, true>(a, st, block) : hipErrorInvalidValue;
+        else
+            return hipErrorInvalidValue;
+    }
+    if (mode == MODE_INV) {
+        if constexpr (NF == 1)  // reads the inverse only
+            return launch_one<P, NF, MODE_INV, false>(a, st, block);
+        else
+            return a.ct ? launch_one<P, NF, MODE_INV, true>(a, st, block)
+                        : launch_one<P, NF, MODE_INV, false>(a, st, block);
+    }
+    return a.ct ? launch_one<P, NF, MODE_DIAG, true>(a, st, block) : launch_one<P, NF, MODE_DIAG, false>(a, st, block);
 }
 
 hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a0, hipStream_t st, int block)
@@ -352,18 +410,9 @@ hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a0, hipSt
         a.r0 = 0;
         a.rg = a.nrhs;
     }
-#define TMX_DS(P, NF)                                                                     \
-    if (prec == P && nf == NF) {                                                          \
-        return mode == MODE_INV ? launch_one<P, NF, MODE_INV>(a, st, block)               \
-                                : launch_one<P, NF, MODE_DIAG>(a, st, block);             \
-    }
-    TMX_DS(F64, 1)
-    TMX_DS(F32, 1)
-    TMX_DS(F16, 1)
-    TMX_DS(F64, 2)
-    TMX_DS(F32, 2)
-    TMX_DS(F16, 2)
-#undef TMX_DS
+    if (prec == F64) return nf == 1 ? launch_mode<F64, 1>(mode, a, st, block) : launch_mode<F64, 2>(mode, a, st, block);
+    if (prec == F32) return nf == 1 ? launch_mode<F32, 1>(mode, a, st, block) : launch_mode<F32, 2>(mode, a, st, block);
+    if (prec == F16) return nf == 1 ? launch_mode<F16, 1>(mode, a, st, block) : launch_mode<F16, 2>(mode, a, st, block);
     return hipErrorInvalidValue;
 }
 

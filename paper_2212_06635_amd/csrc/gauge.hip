@@ -9,8 +9,10 @@
 //    -s_k) (s = Pauli matrices), so each chirality block is
 //      T_chi = i kappa csw (s_1 (x) G_1 + s_2 (x) G_2 + s_3 (x) G_3),
 //      G_1 = -F_yz +- F_xt,  G_2 = F_xz +- F_yt,  G_3 = -F_xy +- F_zt
-//    (+ for chirality 0 = spins 0,1, - for chirality 1).  A = 1 + T is stored
-//    as two Hermitian 6x6 blocks.
+//    (+ for chirality 0 = spins 0,1, - for chirality 1).  T is stored as its
+//    structured blocks (load_ct): H = i kappa csw G_3, K = i kappa csw
+//    (G_1 + i G_2).  A clover term given by the caller is stored as A = 1 + T
+//    in general Hermitian 6x6 blocks.
 //  * site inverses through (A + i nu)^{-1} = (A - i nu)(A^2 + nu^2)^{-1},
 //    with the Hermitian positive A^2 + nu^2 inverted by Cholesky (no
 //    pivoting needed), all in FP64.
@@ -244,7 +246,27 @@ __device__ __forceinline__ void load_herm(const double *clov64, long stride, lon
         }
 }
 
-// clov64 layout: [parity][72 reals as 36 double2][Vh]
+// A = 1 + T of one chirality from the structured (ct) or general storage
+__device__ __forceinline__ void load_block(const double *clov64, int ct, long stride, long s, int chir, cd A[6][6])
+{
+    if (!ct) {
+        load_herm(clov64, stride, s, chir, A);
+        return;
+    }
+    double a[28];
+    load_ct<F64>(clov64, stride, s, chir, a);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        A[i][i] = cd{1.0 + ct_diag(a, i), 0.0};
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+            A[i][j] = ct_lower(a, i, j);
+            A[j][i] = conj(A[i][j]);
+        }
+    }
+}
+
+// clov64 layout: [parity][56 reals as 28 double2][Vh]
 __global__ void clover_build_kernel(const double *links64, double *clov64, Geom g, double kappa, double csw)
 {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -261,31 +283,33 @@ __global__ void clover_build_kernel(const double *links64, double *clov64, Geom 
     M3 Fyt = field_strength(links64, g, x, 1, 3);
     M3 Fzt = field_strength(links64, g, x, 2, 3);
     const double kc = kappa * csw;
-    double *base = clov64 + (size_t)p * 36 * g.Vh * 2;
+    double *base = clov64 + (size_t)p * 28 * g.Vh * 2;
 #pragma unroll
     for (int chir = 0; chir < 2; ++chir) {
         const double sg = chir == 0 ? 1.0 : -1.0;
-        cd A[6][6];
+        // T = i kc [[G3, G1 - i G2], [G1 + i G2, -G3]] = [[H, K^+], [K, -H]]
+        double a[28];
+        a[3] = 0.0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const int k = 3 * a + b;
+            for (int j = 0; j < 3; ++j) {
+                const int k = 3 * i + j;
                 const cd G1 = -Fyz.m[k] + sg * Fxt.m[k];
                 const cd G2 = Fxz.m[k] + sg * Fyt.m[k];
-                const cd G3 = -Fxy.m[k] + sg * Fzt.m[k];
-                // T = i kc [[G3, G1 - i G2], [G1 + i G2, -G3]]
-                const cd t00 = kc * imul(G3);
-                const cd t01 = kc * imul(G1 - imul(G2));
                 const cd t10 = kc * imul(G1 + imul(G2));
-                A[a][b] = t00;
-                A[a][3 + b] = t01;
-                A[3 + a][b] = t10;
-                A[3 + a][3 + b] = -t00;
+                a[10 + 2 * k] = t10.re;
+                a[11 + 2 * k] = t10.im;
+                if (j > i) continue;
+                const cd t00 = kc * imul(-Fxy.m[k] + sg * Fzt.m[k]);
+                if (i == j) {
+                    a[i] = t00.re;
+                } else {
+                    a[4 + 2 * (i + j - 1)] = t00.re;
+                    a[5 + 2 * (i + j - 1)] = t00.im;
+                }
             }
-#pragma unroll
-        for (int i = 0; i < 6; ++i) A[i][i].re += 1.0;
-        store_herm(base, g.Vh, s, chir, A);
+        store_seq<F64, 28>(base + (size_t)chir * 14 * g.Vh * 2, g.Vh, s, a);
     }
 }
 
@@ -298,8 +322,101 @@ hipError_t launch_clover_build(const double *links64, double *clov64, Geom g, do
     return hipGetLastError();
 }
 
+// thread per (even site, chirality): a[3] = 1 if the elimination on A = 1 + T
+// keeps every pivot at 1/8 or more
+__global__ void clover_check_kernel(double *clov_even, long Vh)
+{
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= 2 * Vh) return;
+    const int chir = (int)(t / Vh);
+    const long s = t - chir * Vh;
+    cd A[6][6];
+    load_block(clov_even, 1, Vh, s, chir, A);
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        ok = ok && A[k][k].re >= 0.125;  // false for a NaN too
+        const double d = 1.0 / A[k][k].re;
+#pragma unroll
+        for (int i = k + 1; i < 6; ++i) {
+            const cd f = d * A[i][k];
+#pragma unroll
+            for (int j = k + 1; j <= i; ++j) cmsub(A[i][j], f, conj(A[j][k]));
+        }
+    }
+    clov_even[2 * ((14 * chir + 1) * Vh + s) + 1] = ok ? 1.0 : 0.0;
+}
+
+hipError_t launch_clover_check(double *clov64_even, Geom g, hipStream_t st)
+{
+    const long n = 2L * g.Vh;
+    hipLaunchKernelGGL(clover_check_kernel, dim3((n + 255) / 256), dim3(256), 0, st, clov64_even, (long)g.Vh);
+    return hipGetLastError();
+}
+
+// four reals per thread (one vector of the FP32 / FP16 layout)
+__global__ void convert_ct_kernel(const double *src, void *dst, int prec, long Vh)
+{
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= 28 * Vh) return;  // both parities, both chiralities, 7 vectors
+    const long q = t / Vh, s = t - q * Vh;
+    const double2 *in = reinterpret_cast<const double2 *>(src);
+    const double2 lo = in[2 * q * Vh + s], hi = in[(2 * q + 1) * Vh + s];
+    const float v[4] = {(float)lo.x, (float)lo.y, (float)hi.x, (float)hi.y};
+    if (prec == F32)
+        static_cast<float4 *>(dst)[q * Vh + s] = make_float4(v[0], v[1], v[2], v[3]);
+    else
+        static_cast<uint2 *>(dst)[q * Vh + s] = f_to_h4(v);
+}
+
+hipError_t launch_convert_ct(const double *src, void *dst, int prec, long Vh, hipStream_t st)
+{
+    const long n = 28 * Vh;
+    hipLaunchKernelGGL(convert_ct_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, dst, prec, Vh);
+    return hipGetLastError();
+}
+
+// thread per (parity, site): both chirality blocks of A = 1 + T as 72 halves
+__global__ void __launch_bounds__(256) convert_ct_general16_kernel(const double *src, void *dst, long Vh)
+{
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= 2 * Vh) return;
+    const long p = t / Vh, s = t - p * Vh;
+    float o[72];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        double a[28];
+        load_ct<F64>(src + (size_t)p * 28 * Vh * 2, Vh, s, c, a);
+        float *q = o + 36 * c;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) q[i] = (float)(1.0 + ct_diag(a, i));
+        int k = 6;
+#pragma unroll
+        for (int i = 1; i < 6; ++i)
+#pragma unroll
+            for (int j = 0; j < i; ++j) {
+                const cd l = ct_lower(a, i, j);
+                q[k] = (float)l.re;
+                q[k + 1] = (float)l.im;
+                k += 2;
+            }
+    }
+    // through FP32, like every FP16 field (launch_convert_seq): keep the compiler
+    // from rounding FP64 to binary16 in one step
+#pragma unroll
+    for (int i = 0; i < 72; ++i) asm volatile("" : "+v"(o[i]));
+    store_seq<F16, 72>(static_cast<char *>(dst) + (size_t)p * 72 * 2 * Vh, Vh, s, o);
+}
+
+hipError_t launch_convert_ct_general16(const double *src, void *dst, long Vh, hipStream_t st)
+{
+    hipLaunchKernelGGL(convert_ct_general16_kernel, dim3((unsigned)((2 * Vh + 255) / 256)), dim3(256), 0, st, src, dst,
+                       Vh);
+    return hipGetLastError();
+}
+
 // canonical T: [lex][chir][6][6] complex128, A = 1 + T
-__global__ void clover_from_canon_kernel(const double *canonT, double *clov64, Geom g, int to_canon)
+__global__ void clover_from_canon_kernel(const double *canonT, double *clov64, int ct, Geom g, int to_canon)
 {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 2L * g.Vh) return;
@@ -313,13 +430,13 @@ __global__ void clover_from_canon_kernel(const double *canonT, double *clov64, G
     x[3] = (int)(r / g.L[2]);
     const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
     const int s = cb_index(g, x);
-    double *base = clov64 + (size_t)p * 36 * g.Vh * 2;
+    double *base = clov64 + (size_t)p * (ct ? 28 : 36) * g.Vh * 2;
     const double2 *cin = reinterpret_cast<const double2 *>(canonT) + i * 72;
     double2 *cout = reinterpret_cast<double2 *>(const_cast<double *>(canonT)) + i * 72;
     for (int chir = 0; chir < 2; ++chir) {
         cd A[6][6];
         if (to_canon) {
-            load_herm(base, g.Vh, s, chir, A);
+            load_block(base, ct, g.Vh, s, chir, A);
             for (int a = 0; a < 6; ++a)
                 for (int b = 0; b < 6; ++b) {
                     cd v = A[a][b];
@@ -340,15 +457,15 @@ __global__ void clover_from_canon_kernel(const double *canonT, double *clov64, G
 hipError_t launch_clover_from_canonical(const double *canonT, double *clov64, Geom g, hipStream_t st)
 {
     const long n = 2L * g.Vh;
-    hipLaunchKernelGGL(clover_from_canon_kernel, dim3((n + 127) / 128), dim3(128), 0, st, canonT, clov64, g, 0);
+    hipLaunchKernelGGL(clover_from_canon_kernel, dim3((n + 127) / 128), dim3(128), 0, st, canonT, clov64, 0, g, 0);
     return hipGetLastError();
 }
 
-hipError_t launch_clover_to_canonical(const double *clov64, double *canonT, Geom g, hipStream_t st)
+hipError_t launch_clover_to_canonical(const double *clov64, int ct, double *canonT, Geom g, hipStream_t st)
 {
     const long n = 2L * g.Vh;
     hipLaunchKernelGGL(clover_from_canon_kernel, dim3((n + 127) / 128), dim3(128), 0, st, canonT,
-                       const_cast<double *>(clov64), g, 1);
+                       const_cast<double *>(clov64), ct, g, 1);
     return hipGetLastError();
 }
 
@@ -431,14 +548,14 @@ __device__ __forceinline__ void herm_square_shift(const cd A[6][6], double c, cd
 
 // thread per (even site, chirality); inv64 layout [72 reals per chirality as
 // 36 double2, chirality-major][Vh]
-__global__ void clover_inv_kernel(const double *clov_even, double *inv64, long Vh, double nu)
+__global__ void clover_inv_kernel(const double *clov_even, int ct, double *inv64, long Vh, double nu)
 {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 2 * Vh) return;
     const int chir = (int)(t / Vh);
     const long s = t - chir * Vh;
     cd A[6][6], S[6][6], Si[6][6];
-    load_herm(clov_even, Vh, s, chir, A);
+    load_block(clov_even, ct, Vh, s, chir, A);
     const double tw = chir == 0 ? nu : -nu;  // i nu gamma5 on this chirality
     herm_square_shift(A, tw * tw, S);
     hpd_inverse(S, Si);
@@ -461,32 +578,32 @@ __global__ void clover_inv_kernel(const double *clov_even, double *inv64, long V
     store_seq<F64, 72>(inv64 + (size_t)chir * 36 * Vh * 2, Vh, s, out);
 }
 
-hipError_t launch_clover_inv(const double *clov64_even, double *inv64, Geom g, double nu, hipStream_t st)
+hipError_t launch_clover_inv(const double *clov64_even, int ct, double *inv64, Geom g, double nu, hipStream_t st)
 {
     const long n = 2L * g.Vh;
-    hipLaunchKernelGGL(clover_inv_kernel, dim3((n + 63) / 64), dim3(64), 0, st, clov64_even, inv64, (long)g.Vh,
+    hipLaunchKernelGGL(clover_inv_kernel, dim3((n + 63) / 64), dim3(64), 0, st, clov64_even, ct, inv64, (long)g.Vh,
                        nu);
     return hipGetLastError();
 }
 
-__global__ void clover_inv_nd_kernel(const double *clov_even, double *invnd64, long Vh, double c)
+__global__ void clover_inv_nd_kernel(const double *clov_even, int ct, double *invnd64, long Vh, double c)
 {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 2 * Vh) return;
     const int chir = (int)(t / Vh);
     const long s = t - chir * Vh;
     cd A[6][6], S[6][6], Si[6][6];
-    load_herm(clov_even, Vh, s, chir, A);
+    load_block(clov_even, ct, Vh, s, chir, A);
     herm_square_shift(A, c, S);
     hpd_inverse(S, Si);
     store_herm(invnd64, Vh, s, chir, Si);
 }
 
-hipError_t launch_clover_inv_nd(const double *clov64_even, double *invnd64, Geom g, double nubar, double epst,
+hipError_t launch_clover_inv_nd(const double *clov64_even, int ct, double *invnd64, Geom g, double nubar, double epst,
                                 hipStream_t st)
 {
     const long n = 2L * g.Vh;
-    hipLaunchKernelGGL(clover_inv_nd_kernel, dim3((n + 63) / 64), dim3(64), 0, st, clov64_even, invnd64,
+    hipLaunchKernelGGL(clover_inv_nd_kernel, dim3((n + 63) / 64), dim3(64), 0, st, clov64_even, ct, invnd64,
                        (long)g.Vh, nubar * nubar - epst * epst);
     return hipGetLastError();
 }

@@ -55,7 +55,7 @@ struct Sys {
     int N(SpinorPtr out, SpinorPtr in, int prec, int cols, double *nrm = nullptr)
     {
         gbytes += 2.0 * mhat_bytes_per_site(prec, nf, cols) * c->Vh * 1e-9;
-        return op_mdagm(c, out, in, op, prec, cols, nrm);
+        return op_mdagm(c, out, in, op, prec, cols, nrm, true);
     }
 };
 

@@ -53,6 +53,9 @@ struct LaunchCfg {
     int rg = 0;
 };
 
+// block slot after the three precisions: FP16 blocks holding A itself
+constexpr int F16A = 3;
+
 // learned-preconditioner state (nn.hip)
 struct PcState;
 
@@ -76,9 +79,12 @@ struct tmx_ctx {
     void *links[3] = {nullptr, nullptr, nullptr};
     bool links_ok[3] = {false, false, false};
 
-    // A = 1 + T on both parities, Hermitian packed, per precision
-    void *clov[3] = {nullptr, nullptr, nullptr};
-    bool clov_ok[3] = {false, false, false};
+    // A = 1 + T on both parities, per block slot (a precision, or F16A):
+    // structured blocks when built from the links, general Hermitian ones
+    // when given by the caller; F16A is the general FP16 copy of a clover
+    // term built from the links
+    void *clov[4] = {nullptr, nullptr, nullptr, nullptr};
+    bool clov_ok[4] = {false, false, false, false};
     bool clover_from_host = false;
     double clov_kappa = 0, clov_csw = 0;
 
@@ -148,14 +154,20 @@ void *dev_alloc(tmx_ctx *c, size_t bytes);
 void dev_free(tmx_ctx *c, void *p);
 void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes);
 
-// lazily build everything an apply in `prec` needs
-int ensure_ready(tmx_ctx *c, int prec, bool nd);
+// Site blocks in FP16.  The operator entry points round A = 1 + T and its
+// inverse to binary16, as their callers' fields expect; an iteration inside a
+// solver reads the more accurate and shorter structured T (`inner`), since
+// its solution is that of the FP64 operator either way.  FP64 and FP32 have
+// one form.
+// lazily build everything an apply in `prec` on nrhs right-hand sides needs
+int ensure_ready(tmx_ctx *c, int prec, bool nd, int nrhs = 1, bool inner = false);
 
 // operators on internal fields (asynchronous)
 int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagger, int nrhs);
 // out = N in = Mhat^dagger Mhat in; if nrm is given it receives <in, N in> = |Mhat in|^2
 // of every slot (FP64, Vh * nrhs values)
-int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, double *nrm = nullptr);
+int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, double *nrm = nullptr,
+             bool inner = false);
 int op_D(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec);
 
 // launch shape for a kernel key ("K1_f64", "K2_f32_nd_r12", ...)

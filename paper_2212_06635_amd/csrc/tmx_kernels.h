@@ -8,6 +8,9 @@
 
 namespace tmx {
 
+// what a stencil launch computes (dslash.hip)
+enum { MODE_INV = 0, MODE_DIAG = 1, MODE_SOLVE = 2 };
+
 struct DslashArgs {
     Geom g;
     int parity;        // output parity
@@ -16,7 +19,8 @@ struct DslashArgs {
     SpinorPtr in;      // hopping input (other parity)
     SpinorPtr x;       // diagonal input (output parity), MODE_DIAG only
     LinkPtr U;         // compressed links, both parities
-    const void *clov;  // Hermitian A of the output parity
+    const void *clov;  // A of the output parity: structured blocks (ct) or general Hermitian ones
+    int ct;            // clov holds structured blocks (see load_ct)
     const void *inv;   // MODE_INV: full inverse (deg) or Hermitian inverse factor (nd)
     double nu;         // nu (deg) or nubar (nd), already times 2 kappa
     double epst;       // 2 kappa epsbar (nd)
@@ -54,16 +58,22 @@ hipError_t launch_hop_force(const ForceArgs &f, hipStream_t st);
 hipError_t launch_pack_links(const double *canon, double *links64, Geom g, hipStream_t st);
 // compressed FP64 -> compressed FP32 / FP16 links
 hipError_t launch_convert_links(const double *links64, void *dst, int prec, Geom g, hipStream_t st);
-// clover term A = 1 + T on both parities (Hermitian packed, FP64)
+// clover term A = 1 + T on both parities (structured blocks, FP64)
 hipError_t launch_clover_build(const double *links64, double *clov64, Geom g, double kappa, double csw,
                                hipStream_t st);
+// set the a[3] entries of the even sites' structured FP64 blocks (see load_ct)
+hipError_t launch_clover_check(double *clov64_even, Geom g, hipStream_t st);
+// structured blocks of both parities, FP64 -> FP32 / FP16
+hipError_t launch_convert_ct(const double *src, void *dst, int prec, long Vh, hipStream_t st);
+// structured FP64 blocks of both parities -> general FP16 ones (A = 1 + T rounded)
+hipError_t launch_convert_ct_general16(const double *src, void *dst, long Vh, hipStream_t st);
 // canonical [lex][2][6][6] complex128 -> packed A = 1 + T (FP64)
 hipError_t launch_clover_from_canonical(const double *canonT, double *clov64, Geom g, hipStream_t st);
-hipError_t launch_clover_to_canonical(const double *clov64, double *canonT, Geom g, hipStream_t st);
-// degenerate inverse (A_ee + i nu g5)^{-1}, full 6x6 per chirality (FP64)
-hipError_t launch_clover_inv(const double *clov64_even, double *inv64, Geom g, double nu, hipStream_t st);
+hipError_t launch_clover_to_canonical(const double *clov64, int ct, double *canonT, Geom g, hipStream_t st);
+// degenerate inverse (A_ee + i nu g5)^{-1}, full 6x6 per chirality (FP64); ct: clov64 is structured
+hipError_t launch_clover_inv(const double *clov64_even, int ct, double *inv64, Geom g, double nu, hipStream_t st);
 // two-flavour inverse factor (A_ee^2 + nubar^2 - epst^2)^{-1}, Hermitian packed (FP64)
-hipError_t launch_clover_inv_nd(const double *clov64_even, double *invnd64, Geom g, double nubar, double epst,
+hipError_t launch_clover_inv_nd(const double *clov64_even, int ct, double *invnd64, Geom g, double nubar, double epst,
                                 hipStream_t st);
 // FP64 per-site real sequences -> FP32 / FP16 (n reals per site, Vh sites)
 hipError_t launch_convert_seq(const double *src, void *dst, int prec, int nreal, long nsite, hipStream_t st);
