@@ -434,7 +434,8 @@ static DslashArgs base_args(tmx_ctx *c, int prec, bool nd, int nrhs)
 // K2 on each group of rg right-hand sides, so that a group's neighbour
 // spinors stay in L2 between the two halves)
 static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int prec, bool nd, int nrhs, int sgn,
-                      int g5in, int g5out, double *nrm = nullptr, double rho = 0.0, bool inner = false)
+                      int g5in, int g5out, double rho = 0.0, bool inner = false, const NFuse *first = nullptr,
+                      const NFuse *last = nullptr, SpinorPtr rp = SpinorPtr{})
 {
     const int nf = nd ? 2 : 1;
     const std::string k1 = kname("K1", prec, nd, nrhs), k2 = kname("K2", prec, nd, nrhs);
@@ -459,7 +460,23 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
     b.kfac = c->par.kappa * c->par.kappa;
     b.g5x = g5in;
     b.g5out = g5out;
-    b.nrm = nrm;
+    int k2mode = MODE_DIAG;
+    if (first && first->nrm) {
+        k2mode = MODE_NRM;
+        b.nrm = first->nrm;
+        b.nsig = first->nsig;
+    }
+    if (last && last->res) {
+        k2mode = MODE_RES;
+        b.rin = last->rin;
+        b.rout = last->rout;
+        b.rp = rp;
+        b.rlo = last->rlo;
+        b.rlo_prec = last->lo;
+        b.ralpha = last->alpha;
+        b.rsig = last->sigma;
+        b.nrm = last->rnrm;
+    }
     b.rho = rho;
     b.xcd = l2.xcd;
     b.spt = l2.spt;
@@ -471,7 +488,7 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
         kstat_end(c);
         if (e != hipSuccess) return hip_err(c, e, "K1 launch");
         kstat_begin(c, k2);
-        e = launch_dslash(prec, nf, MODE_DIAG, b, c->stream, l2.block);
+        e = launch_dslash(prec, nf, k2mode, b, c->stream, l2.block);
         kstat_end(c);
         if (e != hipSuccess) return hip_err(c, e, "K2 launch");
     }
@@ -500,7 +517,7 @@ static int mhat_with(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int o
     if (op_is_w(op)) {
         // What^s = g5 Mhat(s) + i s rho~ ; its adjoint is What^-s
         const int s = dagger ? -sgn : sgn;
-        return schur_pair(c, out, in, u, prec, false, nrhs, s, 0, 1, nullptr, w_rho(c, s));
+        return schur_pair(c, out, in, u, prec, false, nrhs, s, 0, 1, w_rho(c, s));
     }
     // Mhat^dagger = g5 Mhat(-sgn) g5
     return schur_pair(c, out, in, u, prec, nd, nrhs, dagger ? -sgn : sgn, dagger, dagger);
@@ -520,7 +537,7 @@ int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagge
     return mhat_with(c, out, in, make_spinor(ud, prec, nf, stride), op, prec, dagger, nrhs);
 }
 
-int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, double *nrm, bool inner)
+int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, const NFuse *fuse, bool inner)
 {
     int r = check_op(c, op);
     if (r) return r;
@@ -535,12 +552,13 @@ int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs
     SpinorPtr u = make_spinor(ud, prec, nf, stride), v = make_spinor(vd, prec, nf, stride);
     const int sgn = op_sign(op);
     // v = g5 Mhat(sgn) in ; out = g5 Mhat(-sgn) v = N in (g5 Mhat(-sgn) g5 is the
-    // adjoint of Mhat(sgn)), so <in, N in> = |v|^2 per slot if nrm is given.
+    // adjoint of Mhat(sgn)), so <in, N in> = |v|^2 per slot.
     // For What: v = What^sgn in, out = What^-sgn v = (What^sgn)^dagger What^sgn in.
     const bool w = op_is_w(op);
-    r = schur_pair(c, v, in, u, prec, nd, nrhs, sgn, 0, 1, nrm, w ? w_rho(c, sgn) : 0.0, inner);
+    r = schur_pair(c, v, in, u, prec, nd, nrhs, sgn, 0, 1, w ? w_rho(c, sgn) : 0.0, inner, fuse);
+    if (!r && fuse && fuse->between) r = fuse->between();
     if (r) return r;
-    return schur_pair(c, out, v, u, prec, nd, nrhs, -sgn, 0, 1, nullptr, w ? w_rho(c, -sgn) : 0.0, inner);
+    return schur_pair(c, out, v, u, prec, nd, nrhs, -sgn, 0, 1, w ? w_rho(c, -sgn) : 0.0, inner, nullptr, fuse, in);
 }
 
 int op_D(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec)

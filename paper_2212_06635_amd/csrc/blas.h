@@ -361,24 +361,33 @@ struct RedWork {
     int max_blocks;
 };
 
-// Launch op over nslot slots with nrhs right-hand sides interleaved; if the
-// op reduces, result[k * NRED + i] (device) receives reduction i of rhs k.
+// block partials of a reducing op only: partials[(b * nrhs + k) * NRED + i] for *nb blocks
 template <class Op>
-hipError_t run_blas(const Op &op, long nslot, int nrhs, const RedWork &w, hipStream_t st)
+hipError_t run_blas_partials(const Op &op, long nslot, int nrhs, const RedWork &w, hipStream_t st, int *nb)
 {
     if (nrhs < 1 || nrhs > MAXR) return hipErrorInvalidValue;
     int m = 1;
     while (2 * m * nrhs <= 256) m *= 2;
     const int block = m * nrhs;
-    long nb = (nslot + block - 1) / block;
-    if (nb > w.max_blocks) nb = w.max_blocks;
-    if (nb < 1) nb = 1;
-    hipLaunchKernelGGL((blas_kernel<Op>), dim3((unsigned)nb), dim3(block), 0, st, op, nslot, nrhs, m, w.partials);
-    hipError_t e = hipGetLastError();
+    long n = (nslot + block - 1) / block;
+    if (n > w.max_blocks) n = w.max_blocks;
+    if (n < 1) n = 1;
+    *nb = (int)n;
+    hipLaunchKernelGGL((blas_kernel<Op>), dim3((unsigned)n), dim3(block), 0, st, op, nslot, nrhs, m, w.partials);
+    return hipGetLastError();
+}
+
+// Launch op over nslot slots with nrhs right-hand sides interleaved; if the
+// op reduces, result[k * NRED + i] (device) receives reduction i of rhs k.
+template <class Op>
+hipError_t run_blas(const Op &op, long nslot, int nrhs, const RedWork &w, hipStream_t st)
+{
+    int nb = 0;
+    hipError_t e = run_blas_partials(op, nslot, nrhs, w, st, &nb);
     if (e != hipSuccess) return e;
     if constexpr (Op::NRED > 0) {
         const int nout = nrhs * Op::NRED;
-        hipLaunchKernelGGL(blas_finish_kernel, dim3(nout), dim3(256), 0, st, w.partials, (int)nb, nout, w.result,
+        hipLaunchKernelGGL(blas_finish_kernel, dim3(nout), dim3(256), 0, st, w.partials, nb, nout, w.result,
                            w.host);
         e = hipGetLastError();
     }

@@ -11,6 +11,12 @@
 //     two flavours: (A + X)^{-1} = (A - X) (A^2 + nubar^2 - epst^2)^{-1},
 //     X = i sgn nubar g5 tau3 - epst tau1, with A and the Hermitian inverse
 //     factor stored.
+//   MODE_NRM (MODE_DIAG that also writes |out|^2 + nsig |x|^2 of every slot).
+//   MODE_RES (MODE_DIAG with a residual epilogue, for the solvers):
+//       rout = rin - alpha (out + sigma p)(s),  nrm = |rout|^2
+//       in FP64: saves the pass that wrote the operator's result and the one
+//       that read it back with r (3 of the 15 spinors of vector traffic in a
+//       CG iteration).
 //   MODE_SOLVE (K1 with the site block inverted in the kernel, one flavour):
 //       out = B_p^{-1}(sgn) (H in)(s) by elimination on the stored A itself.
 //       The stencils are bound by HBM bytes (a wave spends some 130k cycles
@@ -211,6 +217,12 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
     }
 }
 
+template <typename R> __device__ __forceinline__ void add_norm(double &n2, const cx<R> v[6])
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) n2 += (double)v[k].re * v[k].re + (double)v[k].im * v[k].im;
+}
+
 // (A_chir + i tw) v for both flavours (structured or general blocks)
 template <int P, bool CT, typename R>
 __device__ __forceinline__ void apply_clov(const void *clov, long cs, long s, int c, R tw0, const cx<R> *v0, cx<R> *o0,
@@ -256,6 +268,7 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
     // site-block epilogue, one chirality block at a time (register fences
     // keep the two blocks' matrices from being live together)
     cx<R> out[NF][12];
+    double xn2 = 0.0;  // MODE_NRM with nsig: |x|^2
     if constexpr (MODE == MODE_SOLVE) {
         static_assert(CT && NF == 1, "the in-kernel solve takes structured blocks of one flavour");
         const R nb = R(a.sgn * a.nu);
@@ -308,6 +321,7 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                 load_chiral<P>(a.x, 0, t, c, xv);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) xv[k] = gx * xv[k];
+                if (MODE == MODE_NRM && a.nsig) add_norm(xn2, xv);
                 if constexpr (CT) {
                     R b[28];
                     load_ct<P>(a.clov, cs, s, c, b);
@@ -332,6 +346,10 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                     x0[k] = gx * x0[k];
                     x1[k] = gx * x1[k];
                 }
+                if (MODE == MODE_NRM && a.nsig) {
+                    add_norm(xn2, x0);
+                    add_norm(xn2, x1);
+                }
                 apply_clov<P, CT>(a.clov, cs, s, c, tw, x0, out[0] + 6 * c, -tw, x1, out[1] + 6 * c);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
@@ -353,8 +371,42 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
 #pragma unroll
             for (int k = 6; k < 12; ++k) out[f][k] = -out[f][k];
     }
-    if (MODE == MODE_DIAG && a.nrm) {
+    if constexpr (MODE == MODE_RES) {
+        // a kernel of its own: in MODE_DIAG the residual's registers would
+        // take the FP16 kernels from four waves per SIMD to three
+        const double al = a.ralpha ? a.ralpha[rhs] : 1.0, sg = a.rsig ? a.rsig[rhs] : 0.0;
         double n2 = 0.0;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            cx<R> r[12];
+            load_spinor<P, true>(a.rin, f, t, r);
+            if (a.rsig) {
+                cx<R> p[12];
+                load_spinor<P, true>(a.rp, f, t, p);
+#pragma unroll
+                for (int k = 0; k < 12; ++k)
+                    out[f][k] = cx<R>{(R)fma(sg, (double)p[k].re, (double)out[f][k].re),
+                                      (R)fma(sg, (double)p[k].im, (double)out[f][k].im)};
+            }
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                const double re = fma(-al, (double)out[f][k].re, (double)r[k].re);
+                const double im = fma(-al, (double)out[f][k].im, (double)r[k].im);
+                n2 += re * re + im * im;
+                r[k] = cx<R>{(R)re, (R)im};
+            }
+            store_spinor<P, P != F16>(a.rout, f, t, r);
+            if constexpr (P == F64) {
+                if (a.rlo.d && a.rlo_prec == F32) store_spinor<F32>(a.rlo, f, t, r);
+                if (a.rlo.d && a.rlo_prec == F16) store_spinor<F16>(a.rlo, f, t, r);
+            }
+        }
+        a.nrm[t] = n2;
+        return;
+    }
+    if constexpr (MODE == MODE_NRM) {
+        double n2 = 0.0;
+        if (a.nsig) n2 = a.nsig[rhs] * xn2;
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -372,11 +424,12 @@ template <int P, int NF, int MODE, bool CT>
 static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
 {
     const long n = (long)a.g.Vh * (a.rg > 0 ? a.rg : a.nrhs);
-    const long per = block * (long)(a.spt > 0 ? a.spt : 1);
+    const long per = block * (long)(a.spt > 0 && MODE != MODE_RES && MODE != MODE_NRM ? a.spt : 1);
     const int grid = (int)((n + per - 1) / per);
     if (n == 0) return hipSuccess;
-    if (a.spt == 2)
-        hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 2, CT>), dim3(grid), dim3(block), 0, st, a);
+    constexpr int M2 = MODE == MODE_RES || MODE == MODE_NRM ? MODE_DIAG : MODE;
+    if (MODE == M2 && a.spt == 2)
+        hipLaunchKernelGGL((dslash_kernel<P, NF, M2, 2, CT>), dim3(grid), dim3(block), 0, st, a);
     else
         hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 1, CT>), dim3(grid), dim3(block), 0, st, a);
     return hipGetLastError();
@@ -398,6 +451,10 @@ static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int
             return a.ct ? launch_one<P, NF, MODE_INV, true>(a, st, block)
                         : launch_one<P, NF, MODE_INV, false>(a, st, block);
     }
+    if (mode == MODE_NRM)
+        return a.ct ? launch_one<P, NF, MODE_NRM, true>(a, st, block) : launch_one<P, NF, MODE_NRM, false>(a, st, block);
+    if (mode == MODE_RES)
+        return a.ct ? launch_one<P, NF, MODE_RES, true>(a, st, block) : launch_one<P, NF, MODE_RES, false>(a, st, block);
     return a.ct ? launch_one<P, NF, MODE_DIAG, true>(a, st, block) : launch_one<P, NF, MODE_DIAG, false>(a, st, block);
 }
 

@@ -52,10 +52,10 @@ struct Sys {
     }
     // after a group of field() calls: nothing may run on a missing workspace
     int need() const { return nomem ? set_err(c, TMX_ENOMEM, "solver workspace: out of device memory") : TMX_OK; }
-    int N(SpinorPtr out, SpinorPtr in, int prec, int cols, double *nrm = nullptr)
+    int N(SpinorPtr out, SpinorPtr in, int prec, int cols, const NFuse *fuse = nullptr)
     {
         gbytes += 2.0 * mhat_bytes_per_site(prec, nf, cols) * c->Vh * 1e-9;
-        return op_mdagm(c, out, in, op, prec, cols, nrm, true);
+        return op_mdagm(c, out, in, op, prec, cols, fuse, true);
     }
 };
 
@@ -109,19 +109,137 @@ static int apply_shifted(Sys &S, SpinorPtr q, SpinorPtr p, const double *sigma, 
     return pq ? fetch(c, cols, pq) : TMX_OK;  // else the dots stay on the device
 }
 
-// CG step length alpha_k = rho_k / <p, q>_k from the reduction just taken,
-// computed on the device so that the update needs no host round trip;
-// inactive columns (and a vanishing <p, q>) get 0, as on the host before
+// Per right-hand side sums of a per-slot FP64 array: block partials (or, for
+// few slots, the array itself: one launch less) whose layout is
+// part[b * cols + k], summed by the block of each column in the kernel that
+// uses the sum.
+struct SlotPartials {
+    const double *part;
+    int n;  // partials per column
+};
+constexpr long FEW_SLOTS = 8192;
+static int slot_partials(tmx_ctx *c, const double *v, int cols, SlotPartials *out)
+{
+    if (c->Vh <= FEW_SLOTS) {
+        *out = SlotPartials{v, (int)c->Vh};
+        return TMX_OK;
+    }
+    OpSlotSum sum{};
+    sum.v = v;
+    // 512 blocks at most: each thread has several loads in flight, and the
+    // second pass over the partials stays short
+    RedWork w = c->red;
+    w.max_blocks = 512;
+    int nb = 0;
+    HTRY(run_blas_partials(sum, c->Vh * cols, cols, w, c->stream, &nb), "slot sums");
+    *out = SlotPartials{c->red.partials, nb};
+    return TMX_OK;
+}
+
+// sum over b of part[b * cols + k], in the first thread of the (256-thread) block
+static __device__ __forceinline__ double column_sum(const double *part, int n, int cols, int k)
+{
+    __shared__ double sh[256];
+    double s = 0.0;
+    for (int b = threadIdx.x; b < n; b += 256) s += part[(long)b * cols + k];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = 128; h >= 1; h >>= 1) {
+        if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
+        __syncthreads();
+    }
+    return sh[0];
+}
+
+// CG step length alpha_k = rho_k / <p, (N + sigma) p>_k, summed and divided on
+// the device so that the update needs no host round trip; inactive columns
+// (and a vanishing denominator) get 0
 struct AlphaArgs {
     double rho[MAXR];
     int active[MAXR];
-    int cols;
 };
-static __global__ void cg_alpha_kernel(const double *pq, AlphaArgs a, double *alpha)
+static __global__ void __launch_bounds__(256) cg_alpha_kernel(const double *part, int n, AlphaArgs a, double *alpha)
 {
-    const int k = threadIdx.x;
-    if (k < a.cols) alpha[k] = (a.active[k] && pq[k] != 0.0) ? a.rho[k] / pq[k] : 0.0;
+    const int k = blockIdx.x;
+    const double pq = column_sum(part, n, gridDim.x, k);
+    if (threadIdx.x == 0) alpha[k] = (a.active[k] && pq != 0.0) ? a.rho[k] / pq : 0.0;
 }
+
+// column sums into the reduction buffers (read by fetch)
+static __global__ void __launch_bounds__(256) cg_sum_kernel(const double *part, int n, double *result, double *host)
+{
+    const int k = blockIdx.x;
+    const double v = column_sum(part, n, gridDim.x, k);
+    if (threadIdx.x == 0) {
+        result[k] = v;
+        if (host) host[k] = v;
+    }
+}
+static int fetch_slot_sums(tmx_ctx *c, const double *v, int cols, double *out)
+{
+    SlotPartials p;
+    TRY(slot_partials(c, v, cols, &p));
+    hipLaunchKernelGGL(cg_sum_kernel, dim3(cols), dim3(256), 0, c->stream, p.part, p.n, c->red.result, c->red.host);
+    HTRY(hipGetLastError(), "slot sums");
+    return fetch(c, cols, out);
+}
+
+// per right-hand side shifts in device memory
+struct SigmaArgs {
+    double v[MAXR];
+};
+static __global__ void set_sigma_kernel(SigmaArgs a, double *sigma)
+{
+    if (threadIdx.x < MAXR) sigma[threadIdx.x] = a.v[threadIdx.x];
+}
+// *dev = the shifts on the device, or null if there are none
+static int device_sigma(tmx_ctx *c, const double *sigma, int cols, const double **dev)
+{
+    *dev = nullptr;
+    bool any = false;
+    SigmaArgs a{};
+    for (int k = 0; k < cols; ++k) {
+        a.v[k] = sigma ? sigma[k] : 0.0;
+        any = any || a.v[k] != 0.0;
+    }
+    if (!any) return TMX_OK;
+    double *d = static_cast<double *>(ws_get(c, "cg_sigma", sizeof(double) * MAXR));
+    if (!d) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    hipLaunchKernelGGL(set_sigma_kernel, dim3(1), dim3(64), 0, c->stream, a, d);
+    *dev = d;
+    return hip_err(c, hipGetLastError(), "shifts");
+}
+
+// x += a p (do_x) ; p = r + b p (do_p)
+template <int PX, int P> struct OpXp {
+    static constexpr int NRED = 0;
+    SpinorPtr x, p, r;
+    int nf, do_x, do_p;
+    const double *a;  // device
+    double b[MAXR];
+    __device__ void operator()(long t, int k, double *) const
+    {
+        const double ak = a[k], bk = b[k];
+        for (int f = 0; f < nf; ++f) {
+            cd vp[12];
+            ld<P>(p, f, t, vp);
+            if (do_x) {
+                cd vx[12];
+                ld<PX>(x, f, t, vx);
+#pragma unroll
+                for (int c = 0; c < 12; ++c) vx[c] = vx[c] + ak * vp[c];
+                st<PX>(x, f, t, vx);
+            }
+            if (do_p) {
+                cd vr[12];
+                ld<P>(r, f, t, vr);
+#pragma unroll
+                for (int c = 0; c < 12; ++c) vp[c] = vr[c] + bk * vp[c];
+                st<P>(p, f, t, vp);
+            }
+        }
+    }
+};
 
 // preconditioned CG step length alpha = rho / <p, q> on the device (0 for a
 // non-positive <p, q>: breakdown, seen on the host when it reads alpha), also
@@ -143,18 +261,19 @@ static int true_residual(Sys &S, SpinorPtr r, SpinorPtr rlo, bool write_lo, Spin
                          const double *sigma, int cols, double *rr)
 {
     tmx_ctx *c = S.c;
-    SpinorPtr q = S.field("trq", F64, cols);
-    TRY(S.need());
-    TRY(apply_shifted<F64>(S, q, x, sigma, cols, nullptr));
-    OpXmyNorm<F64, F64, F64, PL> o{};
-    o.r = r;
-    o.b = b;
-    o.q = q;
-    o.rlo = rlo;
-    o.nf = S.nf;
-    o.write_lo = write_lo ? 1 : 0;
-    HTRY(run_blas(o, c->Vh * cols, cols, c->red, c->stream), "true residual");
-    return fetch(c, cols, rr);
+    NFuse f{};
+    TRY(device_sigma(c, sigma, cols, &f.sigma));
+    f.rnrm = static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh * cols));
+    if (!f.rnrm) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    f.res = true;
+    f.rin = b;
+    f.rout = r;
+    if (write_lo) {
+        f.rlo = rlo;
+        f.lo = PL;
+    }
+    TRY(S.N(r, x, F64, cols, &f));
+    return fetch_slot_sums(c, f.rnrm, cols, rr);
 }
 
 template <int PD, int PS> static int copy_field(Sys &S, SpinorPtr d, SpinorPtr s, int cols, double *nrm)
@@ -202,35 +321,40 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
     SpinorPtr r = S.field("r", F64, cols);
     SpinorPtr rl = mixed ? S.field("rl", P, cols) : r;
     SpinorPtr p = S.field("p", P, cols);
-    SpinorPtr q = S.field("q", P, cols);
     SpinorPtr xl = mixed ? S.field("xl", F32, cols) : x;
     TRY(S.need());
     double *alpha = static_cast<double *>(ws_get(c, "cg_alpha", sizeof(double) * MAXR));
-    // unshifted: <p, N p> = |Mhat p|^2, summed from the per-slot norms the
-    // operator's first half writes (no separate pass over p and q)
-    bool shifted = false;
-    for (int k = 0; k < cols; ++k) shifted = shifted || (sigma && sigma[k] != 0.0);
-    double *pnrm = shifted ? nullptr : static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh * cols));
-    if (!alpha || (!shifted && !pnrm)) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    // per-slot |Mhat p|^2 + sigma |p|^2 = <p, (N + sigma) p>, then |r|^2: both
+    // written by the operator's own kernels
+    double *nrm = static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh * cols));
+    if (!alpha || !nrm) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    NFuse fuse{};
+    TRY(device_sigma(c, sigma, cols, &fuse.sigma));
+    fuse.nsig = fuse.sigma;
+    fuse.nrm = fuse.rnrm = nrm;
+    fuse.res = true;
+    fuse.rin = fuse.rout = rl;
+    fuse.alpha = alpha;
 
-    double bb[MAXR], rho[MAXR], rho1[MAXR], rmax[MAXR];
+    double bb[MAXR], rho[MAXR], rho1[MAXR], rmax[MAXR], tr[MAXR];
     int active[MAXR], iters[MAXR], nrel[MAXR];
     TRY((copy_field<F64, F64>(S, r, b, cols, bb)));
     for (int k = 0; k < cols; ++k)  // a NaN or infinite entry makes |b|^2 non-finite (x untouched)
         if (!std::isfinite(bb[k])) return set_err(c, TMX_EINVAL, "source with a non-finite entry");
-    if (!x_is_guess) TRY(zero_field<F64>(S, x, cols));
-    // r = b - N x (also for x = 0, to start from an exact residual)
-    TRY(true_residual<P>(S, r, rl, mixed, b, x, sigma, cols, rho));
+    if (x_is_guess) {
+        TRY(true_residual<P>(S, r, rl, mixed, b, x, sigma, cols, rho));
+    } else {  // r = b
+        TRY(zero_field<F64>(S, x, cols));
+        if (mixed) TRY((copy_field<P, F64>(S, rl, r, cols, nullptr)));
+        for (int k = 0; k < cols; ++k) rho[k] = bb[k];
+    }
     if (mixed) TRY(zero_field<F32>(S, xl, cols));
     // p = r (low precision)
-    if (mixed) {
-        TRY((copy_field<P, P>(S, p, rl, cols, nullptr)));
-    } else {
-        TRY((copy_field<P, F64>(S, p, r, cols, nullptr)));
-    }
+    TRY((copy_field<P, P>(S, p, rl, cols, nullptr)));
     int nactive = 0;
     for (int k = 0; k < cols; ++k) {
         rmax[k] = rho[k];
+        tr[k] = rho[k];
         iters[k] = 0;
         nrel[k] = 0;
         active[k] = (bb[k] > 0 && std::sqrt(rho[k]) > tol * std::sqrt(bb[k])) ? 1 : 0;
@@ -238,33 +362,26 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
     }
     const double t0 = now_seconds();
     int it = 0;
+    bool tr_current = true;  // tr holds the true residual of x
     while (nactive > 0 && it < maxiter) {
-        if (shifted) {
-            TRY(apply_shifted<P>(S, q, p, sigma, cols, nullptr));
-        } else {
-            TRY(S.N(q, p, P, cols, pnrm));
-            OpSlotSum sum{};
-            sum.v = pnrm;
-            HTRY(run_blas(sum, c->Vh * cols, cols, c->red, c->stream), "<p, N p>");
-        }
-        ++it;
+        // an iteration: K1, K2 (writes <p, (N + sigma) p>), alpha, K1, K2
+        // (r -= alpha (N + sigma) p, |r|^2), then x and p in one pass: 12
+        // spinors of vector traffic instead of 15
         AlphaArgs aa{};
-        aa.cols = cols;
         for (int k = 0; k < cols; ++k) {
             aa.rho[k] = rho[k];
             aa.active[k] = active[k];
         }
-        hipLaunchKernelGGL(cg_alpha_kernel, dim3(1), dim3(64), 0, c->stream, c->red.result, aa, alpha);
-        HTRY(hipGetLastError(), "cg step length");
-        OpAxpyNorm<mixed ? F32 : F64, P, P, P> up{};
-        up.x = xl;
-        up.p = p;
-        up.r = rl;
-        up.q = q;
-        up.nf = S.nf;
-        up.ad = alpha;
-        HTRY(run_blas(up, c->Vh * cols, cols, c->red, c->stream), "cg update");
-        TRY(fetch(c, cols, rho1));
+        fuse.between = [&]() -> int {
+            SlotPartials sp;
+            TRY(slot_partials(c, nrm, cols, &sp));
+            hipLaunchKernelGGL(cg_alpha_kernel, dim3(cols), dim3(256), 0, c->stream, sp.part, sp.n, aa, alpha);
+            return hip_err(c, hipGetLastError(), "cg step length");
+        };
+        TRY(S.N(rl, p, P, cols, &fuse));
+        ++it;
+        tr_current = false;
+        TRY(fetch_slot_sums(c, nrm, cols, rho1));
         bool reliable = false;
         for (int k = 0; k < cols; ++k) {
             if (!active[k]) continue;
@@ -276,8 +393,17 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
                     reliable = true;
             }
         }
+        OpXp<mixed ? F32 : F64, P> xp{};
+        xp.x = xl;
+        xp.p = p;
+        xp.r = rl;
+        xp.nf = S.nf;
+        xp.a = alpha;
+        xp.do_x = 1;
         if (mixed && reliable) {
             // x += xl ; xl = 0 ; r = b - N x ; rl = r
+            HTRY(run_blas(xp, c->Vh * cols, cols, c->red, c->stream), "cg x update");
+            xp.do_x = 0;
             OpAddTo<F64, F32> ad{};
             ad.x = x;
             ad.y = xl;
@@ -285,26 +411,23 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
             ad.zero_y = 1;
             HTRY(run_blas(ad, c->Vh * cols, cols, c->red, c->stream), "reliable add");
             TRY(true_residual<P>(S, r, rl, true, b, x, sigma, cols, rho1));
+            tr_current = true;
             for (int k = 0; k < cols; ++k) {
+                tr[k] = rho1[k];
                 if (!active[k]) continue;
                 rmax[k] = rho1[k];
                 nrel[k]++;
             }
         }
-        OpAxpby<P, P> px{};
-        px.y = p;
-        px.x = rl;
-        px.nf = S.nf;
         nactive = 0;
         for (int k = 0; k < cols; ++k) {
             if (active[k] && std::sqrt(rho1[k]) <= tol * std::sqrt(bb[k]) && (!mixed || reliable)) active[k] = 0;
-            px.a[k] = 1.0;
-            px.b[k] = active[k] ? rho1[k] / rho[k] : 0.0;
+            xp.b[k] = active[k] ? rho1[k] / rho[k] : 0.0;
             nactive += active[k];
             rho[k] = rho1[k];
         }
-        if (nactive == 0) break;
-        HTRY(run_blas(px, c->Vh * cols, cols, c->red, c->stream), "cg p update");
+        xp.do_p = nactive > 0;
+        if (xp.do_x || xp.do_p) HTRY(run_blas(xp, c->Vh * cols, cols, c->red, c->stream), "cg x, p update");
     }
     if (mixed && nactive > 0) {
         // iteration cap reached mid-way: fold the low-precision increment in
@@ -314,10 +437,10 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
         ad.nf = S.nf;
         ad.zero_y = 1;
         HTRY(run_blas(ad, c->Vh * cols, cols, c->red, c->stream), "final add");
+        tr_current = false;
     }
-    // FP64 true residual
-    double tr[MAXR];
-    TRY(true_residual<P>(S, r, rl, false, b, x, sigma, cols, tr));
+    // FP64 true residual (a last reliable update has just taken it)
+    if (!tr_current) TRY(true_residual<P>(S, r, rl, false, b, x, sigma, cols, tr));
     const double t1 = now_seconds();
     int rc = TMX_OK;
     for (int k = 0; k < cols; ++k) {
@@ -413,8 +536,10 @@ static int pcg_nn_core(Sys &S, SpinorPtr x, SpinorPtr b, const double *sigma, co
     // half when unshifted (as in cg_core); the step length stays on the device
     const bool shifted = sigma && sigma[0] != 0.0;
     double *alpha_d = static_cast<double *>(ws_get(c, "pcg_alpha", sizeof(double)));
-    double *pnrm = shifted ? nullptr : static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh));
-    if (!alpha_d || (!shifted && !pnrm)) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    double *pnrm = static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh));
+    NFuse fuse{};
+    fuse.nrm = pnrm;
+    if (!alpha_d || !pnrm) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
     double bb, rr, rmax, rho, dots[2];
     TRY((copy_field<F64, F64>(S, r, b, 1, &bb)));
     if (!std::isfinite(bb)) return set_err(c, TMX_EINVAL, "source with a non-finite entry");
@@ -447,7 +572,7 @@ static int pcg_nn_core(Sys &S, SpinorPtr x, SpinorPtr b, const double *sigma, co
         if (shifted) {
             TRY(apply_shifted<P>(S, q, p, sigma, 1, nullptr));
         } else {
-            TRY(S.N(q, p, P, 1, pnrm));
+            TRY(S.N(q, p, P, 1, &fuse));
             OpSlotSum sum{};
             sum.v = pnrm;
             HTRY(run_blas(sum, c->Vh, 1, c->red, c->stream), "<p, N p>");

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <functional>
 #include <map>
 #include <string>
 #include <vector>
@@ -164,9 +165,24 @@ int ensure_ready(tmx_ctx *c, int prec, bool nd, int nrhs = 1, bool inner = false
 
 // operators on internal fields (asynchronous)
 int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagger, int nrhs);
-// out = N in = Mhat^dagger Mhat in; if nrm is given it receives <in, N in> = |Mhat in|^2
-// of every slot (FP64, Vh * nrhs values)
-int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, double *nrm = nullptr,
+// What a solver asks of N besides its result (all optional): <in, (N + nsig)
+// in> = |Mhat in|^2 + nsig |in|^2 of every slot in nrm (Vh * nrhs values), and
+// the result taken into a residual instead of `out`,
+//     rout = rin - alpha (N in + sigma in),  rnrm = |rout|^2 of every slot
+// (rlo, if set: a copy in precision lo).  nsig, alpha and sigma are per
+// right-hand side device arrays; alpha null: 1, nsig / sigma null: 0.
+struct NFuse {
+    double *nrm = nullptr;
+    const double *nsig = nullptr;
+    bool res = false;
+    SpinorPtr rin{}, rout{}, rlo{};
+    int lo = 0;
+    const double *alpha = nullptr, *sigma = nullptr;
+    double *rnrm = nullptr;
+    std::function<int()> between;  // called once nrm is enqueued (to enqueue alpha)
+};
+// out = N in = Mhat^dagger Mhat in
+int op_mdagm(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int nrhs, const NFuse *fuse = nullptr,
              bool inner = false);
 int op_D(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec);
 

@@ -323,12 +323,12 @@ __host__ __device__ inline SpinorPtr parity_half(SpinorPtr f, int prec, int nf, 
     return make_spinor(static_cast<char *>(f.d) + spinor_field_bytes(prec, nf, f.stride), prec, nf, f.stride);
 }
 
-template <int P, typename R>
+template <int P, bool NT = false, typename R>
 __device__ __forceinline__ void load_spinor(const SpinorPtr &f, int flav, long s, cx<R> *v)
 {
     R tmp[24];
     const char *base = static_cast<const char *>(f.d) + (size_t)flav * spinor_vecs<P>() * f.stride * 16;
-    load_seq<P, 24>(base, f.stride, s, tmp);
+    load_seq<P, 24, R, NT>(base, f.stride, s, tmp);
     if constexpr (P == F16) {
         const float sc = f.nrm[flav * f.stride + s];
 #pragma unroll

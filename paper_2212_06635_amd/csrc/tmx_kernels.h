@@ -9,7 +9,7 @@
 namespace tmx {
 
 // what a stencil launch computes (dslash.hip)
-enum { MODE_INV = 0, MODE_DIAG = 1, MODE_SOLVE = 2 };
+enum { MODE_INV = 0, MODE_DIAG = 1, MODE_SOLVE = 2, MODE_RES = 3, MODE_NRM = 4 };
 
 struct DslashArgs {
     Geom g;
@@ -29,7 +29,16 @@ struct DslashArgs {
     int t_bc;          // fermion time boundary factor
     int g5in, g5x, g5out;
     int xcd;           // XCD-aware block order
-    double *nrm;       // MODE_DIAG, if set: |out|^2 of every slot (FP64), for <p, N p> = |Mhat p|^2
+    double *nrm;       // MODE_NRM: |out|^2 of every slot (FP64), for <p, N p> = |Mhat p|^2
+    const double *nsig;  // MODE_NRM, if set: per right-hand side sigma, adding sigma |x|^2 (<p, (N + sigma) p>)
+    // MODE_RES: the result goes into a residual instead of `out`:
+    //   rout = rin - ralpha (result + rsig rp),  nrm = |rout|^2 of every slot
+    // (per right-hand side coefficients in device memory; ralpha null: 1,
+    // rsig null: 0), computed in FP64; rin and rout may be the same field.
+    // rlo, if set, gets a second copy in precision rlo_prec.
+    SpinorPtr rin, rout, rp, rlo;
+    int rlo_prec;
+    const double *ralpha, *rsig;
     double rho;        // MODE_DIAG, one flavour: adds i rho x to the final output (after g5out)
     int r0, rg;        // right-hand sides r0 .. r0 + rg - 1 of the nrhs per site (rg = 0: all)
     int spt;           // sites (slots) per thread: 1, or a grid-stride loop over spt of them
