@@ -80,7 +80,16 @@ void dev_free(tmx_ctx *c, void *p)
         (void)hipFree(p);
 }
 
-void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes)
+// give a named scratch buffer back (the stream synchronised by the caller)
+static void ws_drop(tmx_ctx *c, Workspace &w)
+{
+    dev_free(c, w.p);
+    c->ws_bytes -= w.bytes;
+    w.p = nullptr;
+    w.bytes = 0;
+}
+
+static void *ws_take(tmx_ctx *c, const std::string &name, size_t bytes)
 {
     Workspace &w = c->ws[name];
     if (w.bytes >= bytes && w.p) return w.p;
@@ -91,10 +100,7 @@ void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes)
     }
     if (w.p) {
         (void)hipStreamSynchronize(c->stream);
-        dev_free(c, w.p);
-        c->ws_bytes -= w.bytes;
-        w.p = nullptr;
-        w.bytes = 0;
+        ws_drop(c, w);
     }
     w.p = dev_alloc(c, bytes);
     if (w.p) {
@@ -102,6 +108,28 @@ void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes)
         c->ws_bytes += bytes;
     }
     return w.p;
+}
+
+void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes)
+{
+    void *p = ws_take(c, name, bytes);
+    if (p || c->spare_busy) return p;
+    bool any = false;
+    for (auto &kv : c->ws) any = any || (kv.second.spare && kv.second.p);
+    if (!any) return nullptr;
+    (void)hipStreamSynchronize(c->stream);
+    for (auto &kv : c->ws)
+        if (kv.second.spare && kv.second.p) ws_drop(c, kv.second);
+    return ws_take(c, name, bytes);
+}
+
+void *ws_spare(tmx_ctx *c, const std::string &name, size_t bytes)
+{
+    const std::string err = c->err;
+    c->ws[name].spare = true;
+    void *p = ws_take(c, name, bytes);
+    if (!p) c->err = err;
+    return p;
 }
 
 // ---------------------------------------------------------------------------

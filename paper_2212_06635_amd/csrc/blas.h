@@ -76,26 +76,6 @@ struct OpSlotSum {
     __device__ void operator()(long t, int, double *acc) const { acc[0] += v[t]; }
 };
 
-// r -= a q ; |r|^2
-template <int PR, int PQ> struct OpRupdNorm {
-    static constexpr int NRED = 1;
-    SpinorPtr r, q;
-    int nf;
-    double a[MAXR];
-    __device__ void operator()(long t, int k, double *acc) const
-    {
-        for (int f = 0; f < nf; ++f) {
-            cd vr[12], vq[12];
-            ld<PR>(r, f, t, vr);
-            ld<PQ>(q, f, t, vq);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) vr[c] = vr[c] - a[k] * vq[c];
-            st<PR>(r, f, t, vr);
-            acc[0] += nrm2(vr);
-        }
-    }
-};
-
 // y = a x + b y (real a, b per rhs).  A zero coefficient means the operand
 // is not read (as in BLAS): y = a x overwrites y whatever it held, NaN
 // included, so a fresh workspace can be its target.
@@ -262,42 +242,6 @@ template <int PA, int PB> struct OpCdotNorm {
                 acc[1] += s.im;
             }
             acc[2] += nrm2(vb);
-        }
-    }
-};
-
-// Multishift update after the residual update, for every active shift j:
-//   x_j += alpha_j p_j ;  p_j = zeta_j r + beta_j p_j
-// reading r once per site.
-template <int PX, int PP, int PR> struct OpMsUpdate {
-    static constexpr int NRED = 0;
-    SpinorPtr r;
-    void *xd[MAXR];
-    void *pd[MAXR];
-    long stride;
-    int nf, nshift;
-    double alpha[MAXR], zeta[MAXR], beta[MAXR];
-    int active[MAXR];
-    __device__ SpinorPtr mkf(void *d, int prec) const { return make_spinor(d, prec, nf, stride); }
-    __device__ void operator()(long t, int, double *) const
-    {
-        for (int f = 0; f < nf; ++f) {
-            cd vr[12];
-            ld<PR>(r, f, t, vr);
-            for (int j = 0; j < nshift; ++j) {
-                if (!active[j]) continue;
-                const SpinorPtr X = mkf(xd[j], PX), Pp = mkf(pd[j], PP);
-                cd vx[12], vp[12];
-                ld<PX>(X, f, t, vx);
-                ld<PP>(Pp, f, t, vp);
-#pragma unroll
-                for (int c = 0; c < 12; ++c) {
-                    vx[c] = vx[c] + alpha[j] * vp[c];
-                    vp[c] = zeta[j] * vr[c] + beta[j] * vp[c];
-                }
-                st<PX>(X, f, t, vx);
-                st<PP>(Pp, f, t, vp);
-            }
         }
     }
 };

@@ -22,6 +22,7 @@
 #include <cstring>
 #include <functional>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "tmx_ctx.h"
@@ -154,15 +155,32 @@ static __device__ __forceinline__ double column_sum(const double *part, int n, i
 // CG step length alpha_k = rho_k / <p, (N + sigma) p>_k, summed and divided on
 // the device so that the update needs no host round trip; inactive columns
 // (and a vanishing denominator) get 0
+constexpr int ALPHA_SLOT = MAXR * 4 - 1;  // last slot of the pinned reduction buffer
 struct AlphaArgs {
     double rho[MAXR];
     int active[MAXR];
 };
-static __global__ void __launch_bounds__(256) cg_alpha_kernel(const double *part, int n, AlphaArgs a, double *alpha)
+static __global__ void __launch_bounds__(256) cg_alpha_kernel(const double *part, int n, AlphaArgs a, double *alpha,
+                                                              double *host_red)
 {
     const int k = blockIdx.x;
     const double pq = column_sum(part, n, gridDim.x, k);
-    if (threadIdx.x == 0) alpha[k] = (a.active[k] && pq != 0.0) ? a.rho[k] / pq : 0.0;
+    if (threadIdx.x == 0) {
+        const double al = (a.active[k] && pq != 0.0) ? a.rho[k] / pq : 0.0;
+        alpha[k] = al;
+        if (host_red && k == 0) host_red[ALPHA_SLOT] = al;
+    }
+}
+
+// the first column's step length on the host: from the pinned slot (written
+// before the readback just taken), or copied when the buffer is not mapped
+static int host_alpha(tmx_ctx *c, const double *alpha, double *out)
+{
+    if (c->red.host) {
+        *out = c->host_red[ALPHA_SLOT];
+        return TMX_OK;
+    }
+    return hip_err(c, hipMemcpy(out, alpha, sizeof(double), hipMemcpyDeviceToHost), "step length readback");
 }
 
 // column sums into the reduction buffers (read by fetch)
@@ -245,13 +263,12 @@ template <int PX, int P> struct OpXp {
 // non-positive <p, q>: breakdown, seen on the host when it reads alpha), also
 // stored in the last slot of the pinned reduction buffer so that the host
 // reads it with the next readback instead of a round trip of its own
-constexpr int PCG_ALPHA_SLOT = MAXR * 4 - 1;
 static __global__ void pcg_alpha_kernel(const double *pq, double rho, double *alpha, double *host_red)
 {
     if (threadIdx.x == 0) {
         const double a = pq[0] > 0.0 ? rho / pq[0] : 0.0;
         alpha[0] = a;
-        if (host_red) host_red[PCG_ALPHA_SLOT] = a;
+        if (host_red) host_red[ALPHA_SLOT] = a;
     }
 }
 
@@ -375,7 +392,8 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
         fuse.between = [&]() -> int {
             SlotPartials sp;
             TRY(slot_partials(c, nrm, cols, &sp));
-            hipLaunchKernelGGL(cg_alpha_kernel, dim3(cols), dim3(256), 0, c->stream, sp.part, sp.n, aa, alpha);
+            hipLaunchKernelGGL(cg_alpha_kernel, dim3(cols), dim3(256), 0, c->stream, sp.part, sp.n, aa, alpha,
+                               nullptr);
             return hip_err(c, hipGetLastError(), "cg step length");
         };
         TRY(S.N(rl, p, P, cols, &fuse));
@@ -590,14 +608,8 @@ static int pcg_nn_core(Sys &S, SpinorPtr x, SpinorPtr b, const double *sigma, co
         up.ad = alpha_d;
         HTRY(run_blas(up, c->Vh, 1, c->red, c->stream), "pcg update");
         TRY(fetch(c, 1, &rr));
-        // the step length, from the pinned slot (written before the readback
-        // just taken) or copied when the reduction buffer is not mapped
         double alpha = 0.0;
-        if (c->red.host) {
-            alpha = c->host_red[PCG_ALPHA_SLOT];
-        } else {
-            HTRY(hipMemcpy(&alpha, alpha_d, sizeof(double), hipMemcpyDeviceToHost), "pcg step length readback");
-        }
+        TRY(host_alpha(c, alpha_d, &alpha));
         if (!(alpha > 0)) return set_err(c, TMX_ENOCONV, "preconditioned CG breakdown");
         if (!std::isfinite(rr)) return set_err(c, TMX_ENOCONV, "preconditioned CG: non-finite residual");
         rmax = std::max(rmax, rr);
@@ -666,18 +678,149 @@ static int dispatch_cg(Sys &S, int prec, SpinorPtr x, SpinorPtr b, int cols, con
 // --------------------------------------------------------------------------
 // multishift CG (low precision P), x_k accumulated in F32 (F64 when P = F64)
 // --------------------------------------------------------------------------
+// Update of the shifted systems k >= 1 for a batch of m iterations at once,
+//     x_k += alpha_kj p_k ;  p_k = zeta_kj r_j + beta_kj p_k,   j = 0 .. m - 1
+// (r_j the residual after iteration j).  Only the smallest shift's direction
+// enters the operator, so the others may lag: taken every iteration, 12
+// shifts move 48 spinors a slot and iteration, four times the vector traffic
+// of the CG itself; in batches of m each x_k and p_k is read and written once
+// per m iterations and the m residuals once for all shifts (m = 8: 7 spinors
+// an iteration for 12 shifts).  The arithmetic is that of the single steps
+// in FP64, with one rounding to storage per batch.
+constexpr int MS_BATCH = 8;   // iterations per batch
+constexpr int MS_SHIFTS = 16; // shifts per launch (the coefficients travel by value: 3.4 KB)
+struct MsBatch {
+    void *x[MS_SHIFTS], *p[MS_SHIFTS];
+    const void *r[MS_BATCH];
+    int ns, m;
+    double al[MS_SHIFTS][MS_BATCH], ze[MS_SHIFTS][MS_BATCH], be[MS_SHIFTS][MS_BATCH];
+};
+
+// FP64 and FP32 fields are plain arrays of reals and the update is elementwise:
+// one 16-byte vector per thread keeps all m residuals in a few registers
+template <int P>
+static __global__ void __launch_bounds__(256) ms_batch_kernel(MsBatch a, long nvec)
+{
+    using V = std::conditional_t<P == F64, ev_d2, ev_f4>;
+    constexpr int W = P == F64 ? 2 : 4;
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= nvec) return;
+    V r[MS_BATCH];
+#pragma unroll
+    for (int j = 0; j < MS_BATCH; ++j)
+        if (j < a.m) r[j] = __builtin_nontemporal_load(static_cast<const V *>(a.r[j]) + t);
+    for (int k = 0; k < a.ns; ++k) {
+        V *xp = static_cast<V *>(a.x[k]) + t, *pp = static_cast<V *>(a.p[k]) + t;
+        V xv = __builtin_nontemporal_load(xp), pv = __builtin_nontemporal_load(pp);
+        double x[W], p[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            x[i] = xv[i];
+            p[i] = pv[i];
+        }
+#pragma unroll
+        for (int j = 0; j < MS_BATCH; ++j) {
+            if (j >= a.m) break;
+            const double al = a.al[k][j], ze = a.ze[k][j], be = a.be[k][j];
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                x[i] = fma(al, p[i], x[i]);
+                p[i] = fma(be, p[i], ze * (double)r[j][i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            xv[i] = x[i];
+            pv[i] = p[i];
+        }
+        __builtin_nontemporal_store(xv, xp);
+        __builtin_nontemporal_store(pv, pp);
+    }
+}
+
+// FP16 directions and residuals carry one scale per (flavour, slot), so a
+// thread takes a whole slot of one flavour; x_k is FP32
+static __global__ void __launch_bounds__(256) ms_batch16_kernel(MsBatch a, long stride, int nf)
+{
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= stride * nf) return;
+    const int f = (int)(t / stride);
+    const long s = t - f * stride;
+    for (int k = 0; k < a.ns; ++k) {
+        const SpinorPtr X = make_spinor(a.x[k], F32, nf, stride), Q = make_spinor(a.p[k], F16, nf, stride);
+        cd x[12], p[12];
+        load_spinor<F32, true>(X, f, s, x);
+        load_spinor<F16, true>(Q, f, s, p);
+#pragma unroll 1
+        for (int j = 0; j < a.m; ++j) {
+            const SpinorPtr R = make_spinor(const_cast<void *>(a.r[j]), F16, nf, stride);
+            cd r[12];
+            load_spinor<F16>(R, f, s, r);
+            const double al = a.al[k][j], ze = a.ze[k][j], be = a.be[k][j];
+#pragma unroll
+            for (int i = 0; i < 12; ++i) {
+                x[i] = x[i] + al * p[i];
+                p[i] = ze * r[i] + be * p[i];
+            }
+        }
+        store_spinor<F32, true>(X, f, s, x);
+        store_spinor<F16>(Q, f, s, p);
+    }
+}
+
+// what an iteration with the operator in precision prec takes from the
+// context on its first call, taken before any spare buffer
+static int reserve_operator(Sys &S, int prec)
+{
+    tmx_ctx *c = S.c;
+    const size_t fb = spinor_field_bytes(prec, S.nf, c->Vh);
+    TRY(ensure_ready(c, prec, S.nf == 2, 1, true));
+    if (!ws_get(c, "op_u" + std::to_string(prec), fb) || !ws_get(c, "op_v" + std::to_string(prec), fb) ||
+        !ws_get(c, "cg_sigma", sizeof(double) * MAXR))
+        return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    return TMX_OK;
+}
+
+// marks the spare buffers in use for a scope
+struct SpareUse {
+    tmx_ctx *c;
+    bool was;
+    explicit SpareUse(tmx_ctx *c_) : c(c_), was(c_->spare_busy) { c->spare_busy = true; }
+    ~SpareUse() { c->spare_busy = was; }
+};
+
 template <int P>
 static int mscg_core(Sys &S, std::vector<SpinorPtr> &xs, SpinorPtr b64, const double *shifts, int ns, double tol,
                      int maxiter, int *iters_out)
 {
     tmx_ctx *c = S.c;
     constexpr int PX = P == F64 ? F64 : F32;
-    SpinorPtr r = S.field("ms_r", P, 1);
-    SpinorPtr q = S.field("ms_q", P, 1);
+    SpinorPtr r0 = S.field("ms_r", P, 1);
     std::vector<SpinorPtr> ps(ns);
     for (int k = 0; k < ns; ++k) ps[k] = S.field("ms_p" + std::to_string(k), P, 1);
     TRY(S.need());
+    double *alpha = static_cast<double *>(ws_get(c, "cg_alpha", sizeof(double) * MAXR));
+    double *nrm = static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh));
+    if (!alpha || !nrm) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    // residuals of a batch: as many as there is room for, one at the least
+    // (then it is updated in place); one shift needs no others
+    TRY(reserve_operator(S, P));
+    const SpareUse spare(c);
+    std::vector<SpinorPtr> ring{r0};
+    while (ns > 1 && (int)ring.size() < MS_BATCH) {
+        void *d = ws_spare(c, "sv_ms_r" + std::to_string(ring.size()), spinor_field_bytes(P, S.nf, c->Vh));
+        if (!d) break;
+        ring.push_back(make_spinor(d, P, S.nf, c->Vh));
+    }
+    const int m = (int)ring.size();
+    NFuse fuse{};
+    TRY(device_sigma(c, shifts, 1, &fuse.sigma));
+    fuse.nsig = fuse.sigma;
+    fuse.nrm = fuse.rnrm = nrm;
+    fuse.res = true;
+    fuse.alpha = alpha;
     double bb;
+    SpinorPtr r = ring[m - 1];  // current residual
     TRY((copy_field<P, F64>(S, r, b64, 1, &bb)));
     if (!std::isfinite(bb)) return set_err(c, TMX_EINVAL, "source with a non-finite entry");
     for (int k = 0; k < ns; ++k) {
@@ -688,56 +831,104 @@ static int mscg_core(Sys &S, std::vector<SpinorPtr> &xs, SpinorPtr b64, const do
     std::vector<int> active(ns, bb > 0 ? 1 : 0), it_k(ns, 0);
     double aprev = 1.0, bprev = 0.0, rr = bb, best = bb;
     const double s0 = shifts[0];
+    // coefficients of the pending batch (iteration j of it in ring[j])
+    std::vector<double> cal(ns * MS_BATCH), cze(ns * MS_BATCH), cbe(ns * MS_BATCH);
+    std::vector<int> used(ns, 0);
+    int pend = 0;
+    auto flush = [&]() -> int {
+        int k = 1;
+        while (pend > 0 && k < ns) {
+            MsBatch a{};
+            a.m = pend;
+            for (int j = 0; j < pend; ++j) a.r[j] = ring[j].d;
+            for (; k < ns && a.ns < MS_SHIFTS; ++k) {
+                if (!used[k]) continue;
+                a.x[a.ns] = xs[k].d;
+                a.p[a.ns] = ps[k].d;
+                for (int j = 0; j < pend; ++j) {
+                    a.al[a.ns][j] = cal[k * MS_BATCH + j];
+                    a.ze[a.ns][j] = cze[k * MS_BATCH + j];
+                    a.be[a.ns][j] = cbe[k * MS_BATCH + j];
+                }
+                ++a.ns;
+            }
+            if (!a.ns) break;
+            if constexpr (P == F16) {
+                const long n = c->Vh * S.nf;
+                hipLaunchKernelGGL(ms_batch16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, a,
+                                   c->Vh, S.nf);
+            } else {
+                const long n = spinor_field_bytes(P, S.nf, c->Vh) / 16;
+                hipLaunchKernelGGL((ms_batch_kernel<P>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, a,
+                                   n);
+            }
+            HTRY(hipGetLastError(), "ms update");
+        }
+        pend = 0;
+        std::fill(used.begin(), used.end(), 0);
+        return TMX_OK;
+    };
     int it = 0, since_best = 0;
     while (it < maxiter) {
         int na = 0;
         for (int k = 0; k < ns; ++k) na += active[k];
         if (na == 0) break;
-        double pq;
-        TRY(apply_shifted<P>(S, q, ps[0], &s0, 1, &pq));
+        AlphaArgs aa{};
+        aa.rho[0] = rr;
+        aa.active[0] = 1;
+        fuse.between = [&]() -> int {
+            SlotPartials sp;
+            TRY(slot_partials(c, nrm, 1, &sp));
+            hipLaunchKernelGGL(cg_alpha_kernel, dim3(1), dim3(256), 0, c->stream, sp.part, sp.n, aa, alpha,
+                               c->red.host);
+            return hip_err(c, hipGetLastError(), "ms step length");
+        };
+        // r -= a (N + s0) p_0 ; |r|^2
+        fuse.rin = r;
+        fuse.rout = ring[pend];
+        TRY(S.N(fuse.rout, ps[0], P, 1, &fuse));
+        r = fuse.rout;
         ++it;
-        if (!(pq > 0)) return set_err(c, TMX_ENOCONV, "multishift CG: breakdown");
-        const double a = rr / pq;
-        OpMsUpdate<PX, P, P> mu{};
-        mu.r = r;
-        mu.stride = c->Vh;
-        mu.nf = S.nf;
-        mu.nshift = ns;
-        std::vector<double> zn(ns, 0.0);
-        for (int k = 0; k < ns; ++k) {
-            mu.xd[k] = xs[k].d;
-            mu.pd[k] = ps[k].d;
-            mu.active[k] = active[k];
-            if (!active[k]) continue;
-            const double ds = shifts[k] - s0;
-            zn[k] = zeta[k] * zprev[k] * aprev / (a * bprev * (zprev[k] - zeta[k]) + zprev[k] * aprev * (1.0 + ds * a));
-            mu.alpha[k] = zeta[k] != 0.0 ? a * zn[k] / zeta[k] : 0.0;
-        }
-        // r -= a q ; |r|^2
-        OpRupdNorm<P, P> ru{};
-        ru.r = r;
-        ru.q = q;
-        ru.nf = S.nf;
-        ru.a[0] = a;
-        HTRY(run_blas(ru, c->Vh, 1, c->red, c->stream), "ms residual");
-        double rr1;
-        TRY(fetch(c, 1, &rr1));
+        double rr1, a = 0.0;
+        TRY(fetch_slot_sums(c, nrm, 1, &rr1));
+        TRY(host_alpha(c, alpha, &a));
+        if (!(a > 0)) return set_err(c, TMX_ENOCONV, "multishift CG: breakdown");
         if (!std::isfinite(rr1)) return set_err(c, TMX_ENOCONV, "multishift CG: non-finite residual");
         const double bt = rr1 / rr;
         for (int k = 0; k < ns; ++k) {
-            if (!active[k]) continue;
-            mu.zeta[k] = zn[k];
-            mu.beta[k] = zeta[k] != 0.0 ? bt * (zn[k] / zeta[k]) * (zn[k] / zeta[k]) : 0.0;
+            double al = 0.0, ze = 0.0, be = 1.0;  // a shift that has converged keeps its x and p
+            if (active[k]) {
+                const double ds = shifts[k] - s0;
+                const double zn = zeta[k] * zprev[k] * aprev /
+                                  (a * bprev * (zprev[k] - zeta[k]) + zprev[k] * aprev * (1.0 + ds * a));
+                const double q = zeta[k] != 0.0 ? zn / zeta[k] : 0.0;
+                al = a * q;
+                ze = zn;
+                be = bt * q * q;
+                zprev[k] = zeta[k];
+                zeta[k] = zn;
+                it_k[k] = it;
+                used[k] = 1;
+                // residual of shift k is |zeta_k| |r|; drop it once converged
+                if (std::fabs(zn) * std::sqrt(rr1) <= tol * std::sqrt(bb)) active[k] = 0;
+            }
+            cal[k * MS_BATCH + pend] = al;
+            cze[k * MS_BATCH + pend] = ze;
+            cbe[k * MS_BATCH + pend] = be;
         }
-        HTRY(run_blas(mu, c->Vh, 1, c->red, c->stream), "ms update");
-        for (int k = 0; k < ns; ++k) {
-            if (!active[k]) continue;
-            zprev[k] = zeta[k];
-            zeta[k] = zn[k];
-            it_k[k] = it;
-            // residual of shift k is |zeta_k| |r|; drop it once converged
-            if (std::fabs(zeta[k]) * std::sqrt(rr1) <= tol * std::sqrt(bb)) active[k] = 0;
+        if (used[0]) {  // the smallest shift: x_0 += a p_0, p_0 = r + beta p_0 for the next product
+            OpXp<PX, P> xp{};
+            xp.x = xs[0];
+            xp.p = ps[0];
+            xp.r = r;
+            xp.nf = S.nf;
+            xp.a = alpha;
+            xp.b[0] = bt;
+            xp.do_x = 1;
+            xp.do_p = 1;
+            HTRY(run_blas(xp, c->Vh, 1, c->red, c->stream), "ms x_0, p_0 update");
         }
+        if (++pend == m) TRY(flush());
         aprev = a;
         bprev = bt;
         rr = rr1;
@@ -749,6 +940,7 @@ static int mscg_core(Sys &S, std::vector<SpinorPtr> &xs, SpinorPtr b64, const do
             break;
         }
     }
+    TRY(flush());
     for (int k = 0; k < ns; ++k) iters_out[k] = it_k[k];
     return TMX_OK;
 }
