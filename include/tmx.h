@@ -117,7 +117,8 @@ typedef struct {
     double delta;       /* reliable-update trigger (0 => 0.01 FP32, 0.03 FP16 iterations) */
     int restart;        /* FGCR restart length m (0 => 16) */
     int use_initial_guess; /* 1: x holds the start vector on entry */
-    double inner_tol;   /* multishift: low-precision stage tolerance (0 => 1e-6 / 5e-4) */
+    double inner_tol;   /* multishift: low-precision stage tolerance (0 => 1e-6 / 5e-4, or an FP64 stage
+                           to tol where that is faster) */
     int inner_prec;     /* multishift / FGCR inner precision TMX_F32 or TMX_F16 (default F32) */
 } tmx_solver_cfg;
 
@@ -302,7 +303,10 @@ int tmx_solve_mhat(tmx_ctx *ctx, double *x, const double *b, int dagger, const t
  * shift-by-shift refinement).  x is nshift contiguous odd fields.  Low
  * precision multishift CG followed by FP64-reliable refinement per shift
  * (cfg->inner_prec selects F32 or F16 for both stages; TMX_F64 runs the
- * plain FP64 multishift CG).  With cfg->kind = TMX_SOLVER_PCG_NN each
+ * plain FP64 multishift CG).  With five shifts or more (three on small
+ * lattices), cfg->inner_tol = 0 and room for FP64 shift vectors in an eighth
+ * of the device memory, the multishift stage runs in FP64 to cfg->tol,
+ * whatever inner_prec: it is faster there than refining shift by shift.  With cfg->kind = TMX_SOLVER_PCG_NN each
  * shift's refinement is the CG preconditioned by the learned network (set by
  * tmx_pc_set_weights or tmx_pc_train; degenerate op only, TMX_EINVAL
  * otherwise), falling back to mixed-precision CG if it stalls (info fallback

@@ -1064,6 +1064,9 @@ struct ForceFields {
     int nf;
 };
 
+static size_t clover_h_bytes(const tmx_ctx *c) { return (size_t)6 * 9 * 2 * c->Vh * sizeof(double); }
+static size_t clover_ka_bytes(const tmx_ctx *c) { return (size_t)6 * 16 * 2 * c->Vh * sizeof(double); }
+
 // flavour f of an internal FP64 field of nf flavours, as a one-flavour field
 static SpinorPtr flavour_view(SpinorPtr a, long stride, int f)
 {
@@ -1104,6 +1107,15 @@ static int force_fields_internal(tmx_ctx *c, SpinorPtr X, SpinorPtr Y, int op, F
     return e != hipSuccess ? hip_err(c, e, "K1 launch") : TMX_OK;
 }
 
+int force_reserve(tmx_ctx *c, int nf)
+{
+    const size_t fb = spinor_field_bytes(F64, nf, c->Vh);
+    if (!ws_get(c, "hf_u", fb) || !ws_get(c, "hf_w", fb) || !ws_get(c, "cf_h", clover_h_bytes(c)) ||
+        !ws_get(c, "cf_ka", clover_ka_bytes(c)))
+        return set_err(c, TMX_ENOMEM, "force workspace: out of device memory");
+    return TMX_OK;
+}
+
 // force (= or +=) coeff * hopping-term force of Re<Y, Mhat X>, per flavour
 static int hop_force_fields(tmx_ctx *c, double *force, const ForceFields &ff, double coeff, int accumulate)
 {
@@ -1137,8 +1149,8 @@ static int clover_force_fields(tmx_ctx *c, double *force, const ForceFields &ff,
 {
     if (c->clover_from_host)
         return set_err(c, TMX_EINVAL, "the clover force needs the clover term built from the links");
-    void *ph = ws_get(c, "cf_h", (size_t)6 * 9 * 2 * c->Vh * sizeof(double));
-    void *pka = ph ? ws_get(c, "cf_ka", (size_t)6 * 16 * 2 * c->Vh * sizeof(double)) : nullptr;
+    void *ph = ws_get(c, "cf_h", clover_h_bytes(c));
+    void *pka = ph ? ws_get(c, "cf_ka", clover_ka_bytes(c)) : nullptr;
     if (!ph || !pka) return set_err(c, TMX_ENOMEM, "clover force workspace: out of device memory");
     CloverForceArgs f{};
     f.g = c->g;

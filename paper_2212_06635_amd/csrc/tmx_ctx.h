@@ -214,6 +214,8 @@ int cg_fallback(tmx_ctx *c, int op, SpinorPtr x, SpinorPtr b, double tol, int ma
 // plus the clover-term (terms & 2) force, canonical link layout
 int force_internal(tmx_ctx *c, double *force, SpinorPtr X, SpinorPtr Y, int op, double coeff, int accumulate,
                    int terms);
+// take the workspaces of force_internal with both terms
+int force_reserve(tmx_ctx *c, int nf);
 
 // kernel-timing brackets around a launch (no-ops unless enabled)
 void kstat_begin(tmx_ctx *c, const std::string &name);

@@ -40,9 +40,10 @@ def _solve(U, o, nf, shifts, inner, **kw):
 
 @pytest.mark.parametrize("ns", [1, 2, 17, 32])
 @pytest.mark.parametrize("nf,inner", [(1, 0), (1, 1), (1, 2), (2, 0), (2, 1), (2, 2)])
-def test_shift_counts(field, ns, nf, inner):
-    print(f"\n[gpu multishift batch] ns {ns} nf {nf} inner {inner}", flush=True)
-    _solve(*field, nf, np.geomspace(1e-4, 10.0, ns), inner)
+@pytest.mark.parametrize("inner_tol", [0.0, 1e-3])  # a stage tolerance of the caller's keeps the stage in its precision
+def test_shift_counts(field, ns, nf, inner, inner_tol):
+    print(f"\n[gpu multishift batch] ns {ns} nf {nf} inner {inner} inner_tol {inner_tol}", flush=True)
+    _solve(*field, nf, np.geomspace(1e-4, 10.0, ns), inner, inner_tol=inner_tol)
 
 
 @pytest.mark.parametrize("inner", [0, 1, 2])
