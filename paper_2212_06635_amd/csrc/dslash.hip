@@ -47,9 +47,10 @@ namespace tmx {
 
 
 
-// acc += (1 + sgn gamma_mu) * bc * W psi,  W = U (fwd) or U^dagger (bwd)
+// transported half spinor k = bc W h of a hop, h the projection of psi by
+// (1 + sgn gamma_mu), W = U (fwd) or U^dagger (bwd): k0, k1 its two spins
 template <int MU, int SGN, bool DAG, typename R>
-__device__ __forceinline__ void hop_term(const cx<R> u[9], R bc, const cx<R> psi[12], cx<R> acc[12])
+__device__ __forceinline__ void hop_half(const cx<R> u[9], R bc, const cx<R> psi[12], cx<R> k0[3], cx<R> k1[3])
 {
     // half spinor h[spin 0/1][colour]
     cx<R> h0[3], h1[3];
@@ -79,7 +80,6 @@ __device__ __forceinline__ void hop_term(const cx<R> u[9], R bc, const cx<R> psi
         }
     }
     // k = W h
-    cx<R> k0[3], k1[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         k0[a] = cx<R>{0, 0};
@@ -97,11 +97,14 @@ __device__ __forceinline__ void hop_term(const cx<R> u[9], R bc, const cx<R> psi
         k0[a] = bc * k0[a];
         k1[a] = bc * k1[a];
     }
-    // reconstruct: upper += k, lower += sgn * a_mu^dagger k
+}
+
+// lower spins of a hop from its half spinor: (l0, l1) += sgn * a_mu^dagger (k0, k1)
+template <int MU, int SGN, typename R>
+__device__ __forceinline__ void hop_lower(const cx<R> k0[3], const cx<R> k1[3], cx<R> *low)
+{
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        acc[c] = acc[c] + k0[c];
-        acc[3 + c] = acc[3 + c] + k1[c];
         cx<R> l0, l1;
         if constexpr (MU == 0) {
             l0 = imul(k1[c]);
@@ -117,13 +120,27 @@ __device__ __forceinline__ void hop_term(const cx<R> u[9], R bc, const cx<R> psi
             l1 = k1[c];
         }
         if constexpr (SGN > 0) {
-            acc[6 + c] = acc[6 + c] + l0;
-            acc[9 + c] = acc[9 + c] + l1;
+            low[c] = low[c] + l0;
+            low[3 + c] = low[3 + c] + l1;
         } else {
-            acc[6 + c] = acc[6 + c] - l0;
-            acc[9 + c] = acc[9 + c] - l1;
+            low[c] = low[c] - l0;
+            low[3 + c] = low[3 + c] - l1;
         }
     }
+}
+
+// acc += (1 + sgn gamma_mu) * bc * W psi
+template <int MU, int SGN, bool DAG, typename R>
+__device__ __forceinline__ void hop_term(const cx<R> u[9], R bc, const cx<R> psi[12], cx<R> acc[12])
+{
+    cx<R> k0[3], k1[3];
+    hop_half<MU, SGN, DAG>(u, bc, psi, k0, k1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        acc[c] = acc[c] + k0[c];
+        acc[3 + c] = acc[3 + c] + k1[c];
+    }
+    hop_lower<MU, SGN>(k0, k1, acc + 6);
 }
 
 template <int P, typename R>
@@ -420,10 +437,311 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
     for (int f = 0; f < NF; ++f) store_spinor<P, P != F16>(a.out, f, t, out[f]);
 }
 
+// ---------------------------------------------------------------------------
+// split form: four waves per 64 slots, one lattice direction each
+// ---------------------------------------------------------------------------
+// One thread per slot takes its eight hops one direction after the other, each
+// waiting for its loads: some 7 us a launch however few sites there are, and
+// below about three waves per SIMD nothing else hides that.  Here wave w of a
+// workgroup takes both hops of direction w for the same 64 slots and leaves
+// the transported half spinors in LDS; after one barrier waves 0 and 1 sum
+// them in the order of the plain form (the results are the same bit for bit)
+// and finish one chirality each.  Site blocks and the other per-site operands
+// are requested before the barrier.
+template <int P, typename R> struct SplitShared {
+    cx<R> k[8][6][64];    // hop, component of the half spinor, slot
+    float amax[2][64]; // FP16 scales: largest component per chirality
+    double n2[64];        // chirality 1's part of the norm
+};
+
+template <int P, int NF, int MU, typename R>
+__device__ __forceinline__ void split_dir(const DslashArgs &a, const int x[4], int s, long rhs, int h, int lane,
+                                          SplitShared<P, R> *sh)
+{
+    const Geom &g = a.g;
+    const int p = a.parity;
+    int y[4] = {x[0], x[1], x[2], x[3]}, z[4] = {x[0], x[1], x[2], x[3]};
+    R bf = R(1), bb = R(1);
+    if (++y[MU] == g.L[MU]) {
+        y[MU] = 0;
+        if (MU == 3) bf = R(a.t_bc);
+    }
+    if (--z[MU] < 0) {
+        z[MU] = g.L[MU] - 1;
+        if (MU == 3) bb = R(a.t_bc);
+    }
+    const int nf = cb_index(g, y), nb = cb_index(g, z);
+    cx<R> u[9], v[9];
+    load_link<P>(a.U, p, MU, s, u);
+    load_link<P>(a.U, 1 - p, MU, nb, v);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        cx<R> psi[12], k[6];
+        load_spinor_g5<P>(a.in, f, (long)nf * a.nrhs + rhs, a.g5in, psi);
+        hop_half<MU, -1, false>(u, bf, psi, k, k + 3);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sh[f].k[h][c][lane] = k[c];
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        cx<R> psi[12], k[6];
+        load_spinor_g5<P>(a.in, f, (long)nb * a.nrhs + rhs, a.g5in, psi);
+        hop_half<MU, +1, true>(v, bb, psi, k, k + 3);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sh[f].k[h + 1][c][lane] = k[c];
+    }
+}
+
+// sum of the hops for chirality c, in the plain form's order (t, z, y, x)
+template <int MU, int P, typename R>
+__device__ __forceinline__ void split_sum_dir(const SplitShared<P, R> &sh, int h, int lane, int c, cx<R> acc[6])
+{
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        cx<R> k[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) k[i] = sh.k[h + d][i][lane];
+        if (c == 0) {
+#pragma unroll
+            for (int i = 0; i < 6; ++i) acc[i] = acc[i] + k[i];
+        } else if (d == 0) {
+            hop_lower<MU, -1>(k, k + 3, acc);
+        } else {
+            hop_lower<MU, +1>(k, k + 3, acc);
+        }
+    }
+}
+
+// store chirality c (6 components) of flavour f; FP16: `m` the scale of the slot
+template <int P, bool NT, typename R>
+__device__ __forceinline__ void store_chiral(const SpinorPtr &o, int f, long t, int c, const cx<R> v[6], float m)
+{
+    R q[12];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        q[2 * k] = v[k].re;
+        q[2 * k + 1] = v[k].im;
+    }
+    char *base = static_cast<char *>(o.d) + (size_t)f * spinor_vecs<P>() * o.stride * 16;
+    if constexpr (P == F16) {
+        const float inv = m > 0.f ? 1.0f / m : 0.f;
+        float z[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) z[k] = (float)q[k] * inv;
+        uint4 *b = reinterpret_cast<uint4 *>(base);
+        if (c == 0) {  // vector 0 and the first half of vector 1
+            b[t] = f_to_h8(z);
+            *reinterpret_cast<uint2 *>(b + o.stride + t) = f_to_h4(z + 8);
+            o.nrm[f * o.stride + t] = m;
+        } else {  // the second half of vector 1 and vector 2
+            *(reinterpret_cast<uint2 *>(b + o.stride + t) + 1) = f_to_h4(z);
+            b[2 * o.stride + t] = f_to_h8(z + 4);
+        }
+    } else {
+        store_seq<P, 12, R, NT>(base + (size_t)c * (spinor_vecs<P>() / 2) * o.stride * 16, o.stride, t, q);
+    }
+}
+
+template <typename R> __device__ __forceinline__ float chiral_max(const cx<R> v[6])
+{
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) m = fmaxf(m, fmaxf(fabsf((float)v[k].re), fabsf((float)v[k].im)));
+    return m;
+}
+
+template <int P, int NF, int MODE, bool CT>
+__global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
+{
+    using R = typename RealOf<P>::type;
+    extern __shared__ __align__(16) char split_lds[];
+    auto *sh = reinterpret_cast<SplitShared<P, R> *>(split_lds);  // one per flavour
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const long n = (long)a.g.Vh * a.rg;
+    const long u0 = (long)xcd_block(a.xcd) * 64 + lane;
+    const bool live = u0 < n;
+    const long u = live ? u0 : n - 1;  // the last workgroup's spare lanes repeat the last slot
+    const int s = (int)(u / a.rg);
+    const long rhs = a.r0 + (u - (long)s * a.rg);
+    const long t = (long)s * a.nrhs + rhs;
+    const long cs = a.g.Vh;
+    const int c = w;  // chirality of waves 0 and 1 in the second part
+    int x[4];
+    cb_coords(a.g, s, a.parity, x);
+
+    // per-site operands of the second part, requested first
+    R b[28];
+    if (w < 2) {
+        if constexpr (CT && MODE != MODE_INV) load_ct<P>(a.clov, cs, s, c, b);
+    }
+    if (w == 0)
+        split_dir<P, NF, 3>(a, x, s, rhs, 0, lane, sh);
+    else if (w == 1)
+        split_dir<P, NF, 2>(a, x, s, rhs, 2, lane, sh);
+    else if (w == 2)
+        split_dir<P, NF, 1>(a, x, s, rhs, 4, lane, sh);
+    else
+        split_dir<P, NF, 0>(a, x, s, rhs, 6, lane, sh);
+    __syncthreads();
+
+    cx<R> out[NF][6];
+    double n2 = 0.0;
+    if (w < 2) {
+        cx<R> acc[NF][6];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) acc[f][k] = cx<R>{0, 0};
+            split_sum_dir<3>(sh[f], 0, lane, c, acc[f]);
+            split_sum_dir<2>(sh[f], 2, lane, c, acc[f]);
+            split_sum_dir<1>(sh[f], 4, lane, c, acc[f]);
+            split_sum_dir<0>(sh[f], 6, lane, c, acc[f]);
+        }
+        const R nb = R(a.sgn * a.nu), tw = c == 0 ? nb : -nb, ep = R(a.epst);
+        if constexpr (MODE == MODE_SOLVE) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) out[0][k] = acc[0][k];
+            ct_solve(b, tw, out[0]);
+        } else if constexpr (MODE == MODE_INV) {
+            if constexpr (NF == 1) {
+                full_apply<P>(a.inv, cs, s, c, a.sgn < 0, acc[0], out[0]);
+            } else {
+                cx<R> t0[6], t1[6];
+                herm_apply_c<P>(a.inv, cs, s, c, R(0), acc[0], t0);
+                herm_apply_c<P>(a.inv, cs, s, c, R(0), acc[1], t1);
+                apply_clov<P, CT>(a.clov, cs, s, c, -tw, t0, out[0], tw, t1, out[1]);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    out[0][k] = out[0][k] + ep * t1[k];
+                    out[1][k] = out[1][k] + ep * t0[k];
+                }
+            }
+        } else {
+            const R kf = R(a.kfac);
+            const R gx = (c == 1 && a.g5x) ? R(-1) : R(1);
+            double xn2 = 0.0;
+            cx<R> xv[NF][6];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                load_chiral<P>(a.x, f, t, c, xv[f]);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) xv[f][k] = gx * xv[f][k];
+                if (MODE == MODE_NRM && a.nsig) add_norm(xn2, xv[f]);
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const R tf = f == 0 ? tw : -tw;
+                if constexpr (CT)
+                    ct_apply(b, tf, xv[f], out[f]);
+                else
+                    herm_apply_c<P>(a.clov, cs, s, c, tf, xv[f], out[f]);
+            }
+            if constexpr (NF == 1) {
+                if (a.rho != 0.0) {
+                    const R rs = (c == 1 && a.g5out) ? R(-a.rho) : R(a.rho);
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) out[0][k] = out[0][k] + rs * imul(gx * xv[0][k]);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    out[0][k] = out[0][k] - ep * xv[1][k];
+                    out[1][k] = out[1][k] - ep * xv[0][k];
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) out[f][k] = out[f][k] - kf * acc[f][k];
+            if (MODE == MODE_NRM && a.nsig) n2 = a.nsig[rhs] * xn2;
+        }
+        if (a.g5out && c == 1) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) out[f][k] = -out[f][k];
+        }
+        if constexpr (MODE == MODE_RES) {
+            const double al = a.ralpha ? a.ralpha[rhs] : 1.0, sg = a.rsig ? a.rsig[rhs] : 0.0;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                cx<R> r[6];
+                load_chiral<P>(a.rin, f, t, c, r);
+                if (a.rsig) {
+                    cx<R> p[6];
+                    load_chiral<P>(a.rp, f, t, c, p);
+#pragma unroll
+                    for (int k = 0; k < 6; ++k)
+                        out[f][k] = cx<R>{(R)fma(sg, (double)p[k].re, (double)out[f][k].re),
+                                          (R)fma(sg, (double)p[k].im, (double)out[f][k].im)};
+                }
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    const double re = fma(-al, (double)out[f][k].re, (double)r[k].re);
+                    const double im = fma(-al, (double)out[f][k].im, (double)r[k].im);
+                    n2 += re * re + im * im;
+                    out[f][k] = cx<R>{(R)re, (R)im};
+                }
+            }
+        } else if constexpr (MODE == MODE_NRM) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) add_norm(n2, out[f]);
+        }
+        if constexpr (P == F16 || MODE == MODE_RES) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) sh[f].amax[c][lane] = chiral_max(out[f]);
+        }
+        if constexpr (MODE == MODE_RES || MODE == MODE_NRM) {
+            if (c == 1) sh[0].n2[lane] = n2;
+        }
+    }
+    if constexpr (P == F16 || MODE == MODE_RES || MODE == MODE_NRM) __syncthreads();
+    if (w >= 2 || !live) return;
+    if constexpr (MODE == MODE_RES || MODE == MODE_NRM) {
+        if (c == 0) a.nrm[t] = n2 + sh[0].n2[lane];
+    }
+    const SpinorPtr dst = MODE == MODE_RES ? a.rout : a.out;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        float m = 0.f;
+        if constexpr (P == F16 || MODE == MODE_RES) m = fmaxf(sh[f].amax[0][lane], sh[f].amax[1][lane]);
+        store_chiral<P, P != F16>(dst, f, t, c, out[f], m);
+        if constexpr (P == F64 && MODE == MODE_RES) {
+            if (a.rlo.d && a.rlo_prec == F32) store_chiral<F32, false>(a.rlo, f, t, c, out[f], m);
+            if (a.rlo.d && a.rlo_prec == F16) store_chiral<F16, false>(a.rlo, f, t, c, out[f], m);
+        }
+    }
+}
+
+// Slots up to which the split form is the faster one.  Measured on N (two K1,
+// two K2; us, plain -> split), one flavour FP64 / FP32 / FP16, then two flavours:
+//    2048 slots  31 -> 23 / 28 -> 20 / 33 -> 23   46 -> 31 / 40 -> 30 / 49 -> 30
+//   13824 slots  40 -> 30 / 34 -> 23 / 36 -> 24   65 -> 44 / 47 -> 35 / 56 -> 34
+//   32768 slots  55 -> 54 / 39 -> 34 / 41 -> 29   86 -> 88 / 56 -> 47 / 63 -> 43
+//   65536 slots  92 -> 99 / 51 -> 53 / 48 -> 42  158 -> 166 / 80 -> 92 / 73 -> 74
+//  120960 slots 158 -> 180 / 86 -> 91 / 66 -> 69
+// (beyond, the plain form's waves fill the chip and LDS and barriers only cost)
+template <int P, int NF> static bool use_split(long n)
+{
+    return n <= (P == F64 ? 24576 : (P == F16 && NF == 1 ? 98304 : 49152));
+}
+
+template <int P, int NF, int MODE, bool CT>
+static hipError_t launch_split(const DslashArgs &a, hipStream_t st)
+{
+    using R = typename RealOf<P>::type;
+    const long n = (long)a.g.Vh * a.rg;
+    const int grid = (int)((n + 63) / 64);
+    hipLaunchKernelGGL((dslash_split_kernel<P, NF, MODE, CT>), dim3(grid), dim3(256), NF * sizeof(SplitShared<P, R>), st,
+                       a);
+    return hipGetLastError();
+}
+
 template <int P, int NF, int MODE, bool CT>
 static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
 {
     const long n = (long)a.g.Vh * (a.rg > 0 ? a.rg : a.nrhs);
+    if (n > 0 && use_split<P, NF>(n)) return launch_split<P, NF, MODE, CT>(a, st);
     const long per = block * (long)(a.spt > 0 && MODE != MODE_RES && MODE != MODE_NRM ? a.spt : 1);
     const int grid = (int)((n + per - 1) / per);
     if (n == 0) return hipSuccess;
