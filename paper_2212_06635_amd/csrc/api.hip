@@ -246,7 +246,6 @@ static int ensure_clover(tmx_ctx *c, int slot)
         double *cl = static_cast<double *>(c->clov[F64]);
         r = hip_err(c, launch_clover_build((const double *)c->links[F64], cl, c->g, c->par.kappa, c->par.csw, c->stream),
                     "clover build");
-        if (!r) r = hip_err(c, launch_clover_check(cl, c->g, c->stream), "clover check");
         if (r) return r;
         c->clov_ok[F64] = true;
         c->clov_kappa = c->par.kappa;

@@ -147,7 +147,7 @@ __device__ __forceinline__ M3 link_at(const double *links64, const Geom &g, cons
     const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
     LinkPtr U{links64, g.Vh};
     M3 u;
-    load_link<F64>(U, p, mu, cb_index(g, x), u.m);
+    load_link<F64, false>(U, p, mu, cb_index(g, x), u.m);
     return u;
 }
 
@@ -160,8 +160,12 @@ __device__ __forceinline__ void step(const Geom &g, const int x[4], int mu, int 
     if (y[mu] >= g.L[mu]) y[mu] -= g.L[mu];
 }
 
-// F_{mu nu}(x) = (Q - Q^+)/8 with Q the sum of the four leaves
-__device__ M3 field_strength(const double *U, const Geom &g, const int x[4], int mu, int nu)
+// F_{mu nu}(x) = (Q - Q^+)/8 with Q the sum of the four leaves.  Q and Q^+
+// enter alike, so a leaf may be replaced by minus its adjoint: two leaves then
+// end in the same link and share its product (10 products instead of 12).
+// f: the imaginary parts of the diagonal of F, then F_10, F_20, F_21.
+__device__ __forceinline__ void field_strength(const double *U, const Geom &g, const int x[4], int mu, int nu,
+                                               double f[9])
 {
     int xpm[4], xpn[4], xmm[4], xmn[4], xmmpn[4], xmmmn[4], xpmmn[4];
     step(g, x, mu, +1, xpm);
@@ -172,43 +176,38 @@ __device__ M3 field_strength(const double *U, const Geom &g, const int x[4], int
     step(g, xmm, nu, -1, xmmmn);
     step(g, xpm, nu, -1, xpmmn);
     M3 Q;
+    const M3 un = link_at(U, g, x, nu), vn = link_at(U, g, xmn, nu);
     {
-        // leaf in the (+mu,+nu) quadrant
-        M3 a = mul(link_at(U, g, x, mu), link_at(U, g, xpm, nu));
-        M3 b = mul_nd(a, link_at(U, g, xpn, mu));
-        Q = mul_nd(b, link_at(U, g, x, nu));
+        // [U_nu(x-nu)^+ U_mu(x-nu) U_nu(x+mu-nu) - U_nu(x) U_mu(x+nu) U_nu(x+mu)^+] U_mu(x)^+
+        M3 s = mul(mul_dn(vn, link_at(U, g, xmn, mu)), link_at(U, g, xpmmn, nu));
+        const M3 t = mul_nd(mul(un, link_at(U, g, xpn, mu)), link_at(U, g, xpm, nu));
+#pragma unroll
+        for (int k = 0; k < 9; ++k) s.m[k] = s.m[k] - t.m[k];
+        Q = mul_nd(s, link_at(U, g, x, mu));
     }
     {
-        // (-mu,+nu): U_nu(x) U_mu(x-mu+nu)^+ U_nu(x-mu)^+ U_mu(x-mu)
-        M3 a = mul_nd(link_at(U, g, x, nu), link_at(U, g, xmmpn, mu));
-        M3 b = mul_nd(a, link_at(U, g, xmm, nu));
-        M3 c = mul(b, link_at(U, g, xmm, mu));
+        // [U_nu(x) U_mu(x-mu+nu)^+ U_nu(x-mu)^+ - U_nu(x-nu)^+ U_mu(x-mu-nu)^+ U_nu(x-mu-nu)] U_mu(x-mu)
+        M3 s = mul_nd(mul_nd(un, link_at(U, g, xmmpn, mu)), link_at(U, g, xmm, nu));
+        const M3 w = mul(link_at(U, g, xmmmn, mu), vn);  // (U_mu U_nu)^+ = U_nu^+ U_mu^+
+        const M3 t = mul_dn(w, link_at(U, g, xmmmn, nu));
 #pragma unroll
-        for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + c.m[k];
+        for (int k = 0; k < 9; ++k) s.m[k] = s.m[k] - t.m[k];
+        const M3 r = mul(s, link_at(U, g, xmm, mu));
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + r.m[k];
     }
-    {
-        // (-mu,-nu): U_mu(x-mu)^+ U_nu(x-mu-nu)^+ U_mu(x-mu-nu) U_nu(x-nu)
-        //          = (U_nu(x-mu-nu) U_mu(x-mu))^+ U_mu(x-mu-nu) U_nu(x-nu)
-        M3 a = mul(link_at(U, g, xmmmn, nu), link_at(U, g, xmm, mu));
-        M3 b = mul_dn(a, link_at(U, g, xmmmn, mu));
-        M3 c = mul(b, link_at(U, g, xmn, nu));
 #pragma unroll
-        for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + c.m[k];
-    }
-    {
-        // (+mu,-nu): U_nu(x-nu)^+ U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^+
-        M3 a = mul_dn(link_at(U, g, xmn, nu), link_at(U, g, xmn, mu));
-        M3 b = mul(a, link_at(U, g, xpmmn, nu));
-        M3 c = mul_nd(b, link_at(U, g, x, mu));
+    for (int i = 0; i < 3; ++i) f[i] = 0.25 * Q.m[4 * i].im;
+    int k = 3;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + c.m[k];
-    }
-    M3 F;
+    for (int i = 1; i < 3; ++i)
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) F.m[3 * i + j] = 0.125 * (Q.m[3 * i + j] - conj(Q.m[3 * j + i]));
-    return F;
+        for (int j = 0; j < i; ++j) {
+            const cd v = 0.125 * (Q.m[3 * i + j] - conj(Q.m[3 * j + i]));
+            f[k] = v.re;
+            f[k + 1] = v.im;
+            k += 2;
+        }
 }
 
 // packed Hermitian store: 36 reals per chirality (d0..d5, 15 lower (re,im))
@@ -266,72 +265,16 @@ __device__ __forceinline__ void load_block(const double *clov64, int ct, long st
     }
 }
 
-// clov64 layout: [parity][56 reals as 28 double2][Vh]
-__global__ void clover_build_kernel(const double *links64, double *clov64, Geom g, double kappa, double csw)
+// whether elimination on 1 + T (structured block a) keeps every pivot at 1/8 or more
+__device__ __forceinline__ bool pivots_bounded(const double a[28])
 {
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2L * g.Vh) return;
-    const int p = (int)(t / g.Vh);
-    const int s = (int)(t - (long)p * g.Vh);
-    int x[4];
-    cb_coords(g, s, p, x);
-    // plane order: xy, xz, xt, yz, yt, zt
-    M3 Fxy = field_strength(links64, g, x, 0, 1);
-    M3 Fxz = field_strength(links64, g, x, 0, 2);
-    M3 Fxt = field_strength(links64, g, x, 0, 3);
-    M3 Fyz = field_strength(links64, g, x, 1, 2);
-    M3 Fyt = field_strength(links64, g, x, 1, 3);
-    M3 Fzt = field_strength(links64, g, x, 2, 3);
-    const double kc = kappa * csw;
-    double *base = clov64 + (size_t)p * 28 * g.Vh * 2;
-#pragma unroll
-    for (int chir = 0; chir < 2; ++chir) {
-        const double sg = chir == 0 ? 1.0 : -1.0;
-        // T = i kc [[G3, G1 - i G2], [G1 + i G2, -G3]] = [[H, K^+], [K, -H]]
-        double a[28];
-        a[3] = 0.0;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const int k = 3 * i + j;
-                const cd G1 = -Fyz.m[k] + sg * Fxt.m[k];
-                const cd G2 = Fxz.m[k] + sg * Fyt.m[k];
-                const cd t10 = kc * imul(G1 + imul(G2));
-                a[10 + 2 * k] = t10.re;
-                a[11 + 2 * k] = t10.im;
-                if (j > i) continue;
-                const cd t00 = kc * imul(-Fxy.m[k] + sg * Fzt.m[k]);
-                if (i == j) {
-                    a[i] = t00.re;
-                } else {
-                    a[4 + 2 * (i + j - 1)] = t00.re;
-                    a[5 + 2 * (i + j - 1)] = t00.im;
-                }
-            }
-        store_seq<F64, 28>(base + (size_t)chir * 14 * g.Vh * 2, g.Vh, s, a);
-    }
-}
-
-hipError_t launch_clover_build(const double *links64, double *clov64, Geom g, double kappa, double csw,
-                               hipStream_t st)
-{
-    const long n = 2L * g.Vh;
-    hipLaunchKernelGGL(clover_build_kernel, dim3((n + 127) / 128), dim3(128), 0, st, links64, clov64, g, kappa,
-                       csw);
-    return hipGetLastError();
-}
-
-// thread per (even site, chirality): a[3] = 1 if the elimination on A = 1 + T
-// keeps every pivot at 1/8 or more
-__global__ void clover_check_kernel(double *clov_even, long Vh)
-{
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * Vh) return;
-    const int chir = (int)(t / Vh);
-    const long s = t - chir * Vh;
     cd A[6][6];
-    load_block(clov_even, 1, Vh, s, chir, A);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        A[i][i] = cd{1.0 + ct_diag(a, i), 0.0};
+#pragma unroll
+        for (int j = 0; j < i; ++j) A[i][j] = ct_lower(a, i, j);
+    }
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -344,13 +287,77 @@ __global__ void clover_check_kernel(double *clov_even, long Vh)
             for (int j = k + 1; j <= i; ++j) cmsub(A[i][j], f, conj(A[j][k]));
         }
     }
-    clov_even[2 * ((14 * chir + 1) * Vh + s) + 1] = ok ? 1.0 : 0.0;
+    return ok;
 }
 
-hipError_t launch_clover_check(double *clov64_even, Geom g, hipStream_t st)
+// clov64 layout: [parity][56 reals as 28 double2][Vh].  Six waves per 64 sites
+// of one parity, one plane each (a thread that took all six planes held the
+// results of five while computing the sixth: 1.6 kB of scratch a lane); the
+// nine reals of each F meet in LDS and two waves write one chirality each.
+// The links are read through the caches (each serves 24 plaquette leaves of
+// its neighbourhood) with both parities of a region on one XCD: 4.74 -> 1.68 ms
+// at 32^3x64 (2.19 ms with streaming loads and no XCD order), 314 -> 96 us at
+// 16^3x32.
+__global__ void __launch_bounds__(384) clover_build_kernel(const double *links64, double *clov64, Geom g, double kappa,
+                                                           double csw)
 {
-    const long n = 2L * g.Vh;
-    hipLaunchKernelGGL(clover_check_kernel, dim3((n + 255) / 256), dim3(256), 0, st, clov64_even, (long)g.Vh);
+    __shared__ double F[6][9][64];  // plane order: xy, xz, xt, yz, yt, zt
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int b = xcd_block(1), p = b & 1;  // both parities of a region on one XCD
+    const int s0 = (b >> 1) * 64 + lane;
+    const int s = s0 < g.Vh ? s0 : g.Vh - 1;
+    int x[4];
+    cb_coords(g, s, p, x);
+    {
+        const int mu = w < 3 ? 0 : (w < 5 ? 1 : 2), nu = w < 3 ? w + 1 : (w < 5 ? w - 1 : 3);
+        double f[9];
+        field_strength(links64, g, x, mu, nu, f);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) F[w][k][lane] = f[k];
+    }
+    __syncthreads();
+    if (w >= 2 || s0 >= g.Vh) return;
+    const double kc = kappa * csw, sg = w == 0 ? 1.0 : -1.0;
+    double g1[9], g2[9], g3[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        g1[k] = -F[3][k][lane] + sg * F[2][k][lane];
+        g2[k] = F[1][k][lane] + sg * F[4][k][lane];
+        g3[k] = -F[0][k][lane] + sg * F[5][k][lane];
+    }
+    // T = i kc [[G3, G1 - i G2], [G1 + i G2, -G3]] = [[H, K^+], [K, -H]]
+    double a[28];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        a[i] = -kc * g3[i];
+        a[4 + 2 * i] = -kc * g3[4 + 2 * i];
+        a[5 + 2 * i] = kc * g3[3 + 2 * i];
+        // K_ii = kc (i G1 - G2)_ii
+        a[10 + 8 * i] = -kc * g1[i];
+        a[11 + 8 * i] = -kc * g2[i];
+    }
+    int k = 3;
+#pragma unroll
+    for (int i = 1; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+            const int lo = 10 + 2 * (3 * i + j), up = 10 + 2 * (3 * j + i);
+            a[lo] = kc * (-g1[k + 1] - g2[k]);
+            a[lo + 1] = kc * (g1[k] - g2[k + 1]);
+            a[up] = kc * (-g1[k + 1] + g2[k]);  // G_ji = -conj(G_ij)
+            a[up + 1] = kc * (-g1[k] - g2[k + 1]);
+            k += 2;
+        }
+    a[3] = 0.0;
+    if (p == 0 && pivots_bounded(a)) a[3] = 1.0;
+    store_seq<F64, 28>(clov64 + ((size_t)p * 28 + w * 14) * g.Vh * 2, g.Vh, s, a);
+}
+
+hipError_t launch_clover_build(const double *links64, double *clov64, Geom g, double kappa, double csw,
+                               hipStream_t st)
+{
+    const long nb = 2L * ((g.Vh + 63) / 64);
+    hipLaunchKernelGGL(clover_build_kernel, dim3((unsigned)nb), dim3(384), 0, st, links64, clov64, g, kappa, csw);
     return hipGetLastError();
 }
 
@@ -416,7 +423,7 @@ hipError_t launch_convert_ct_general16(const double *src, void *dst, long Vh, hi
 }
 
 // canonical T: [lex][chir][6][6] complex128, A = 1 + T
-__global__ void clover_from_canon_kernel(const double *canonT, double *clov64, int ct, Geom g, int to_canon)
+__global__ void __launch_bounds__(128) clover_from_canon_kernel(const double *canonT, double *clov64, int ct, Geom g, int to_canon)
 {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 2L * g.Vh) return;
@@ -548,7 +555,7 @@ __device__ __forceinline__ void herm_square_shift(const cd A[6][6], double c, cd
 
 // thread per (even site, chirality); inv64 layout [72 reals per chirality as
 // 36 double2, chirality-major][Vh]
-__global__ void clover_inv_kernel(const double *clov_even, int ct, double *inv64, long Vh, double nu)
+__global__ void __launch_bounds__(64) clover_inv_kernel(const double *clov_even, int ct, double *inv64, long Vh, double nu)
 {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 2 * Vh) return;
@@ -586,7 +593,7 @@ hipError_t launch_clover_inv(const double *clov64_even, int ct, double *inv64, G
     return hipGetLastError();
 }
 
-__global__ void clover_inv_nd_kernel(const double *clov_even, int ct, double *invnd64, long Vh, double c)
+__global__ void __launch_bounds__(64) clover_inv_nd_kernel(const double *clov_even, int ct, double *invnd64, long Vh, double c)
 {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 2 * Vh) return;

@@ -373,7 +373,8 @@ struct LinkPtr {
 template <int P> __host__ __device__ constexpr int link_vecs() { return P == F64 ? 6 : 3; }
 template <int P> __host__ __device__ constexpr int link_vec_bytes() { return P == F16 ? 8 : 16; }
 
-template <int P, typename R>
+// NT = false where neighbouring sites read the same links again
+template <int P, bool NT = true, typename R>
 __device__ __forceinline__ void load_link(const LinkPtr &U, int p, int mu, long s, cx<R> u[9])
 {
     R t[12];
@@ -382,7 +383,7 @@ __device__ __forceinline__ void load_link(const LinkPtr &U, int p, int mu, long 
         const double2 *b = static_cast<const double2 *>(U.d) + base;
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            double2 v = ldv<true>(b + k * U.Vh + s);
+            double2 v = ldv<NT>(b + k * U.Vh + s);
             t[2 * k] = v.x;
             t[2 * k + 1] = v.y;
         }
@@ -390,7 +391,7 @@ __device__ __forceinline__ void load_link(const LinkPtr &U, int p, int mu, long 
         const float4 *b = static_cast<const float4 *>(U.d) + base;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            float4 v = ldv<true>(b + k * U.Vh + s);
+            float4 v = ldv<NT>(b + k * U.Vh + s);
             t[4 * k] = v.x;
             t[4 * k + 1] = v.y;
             t[4 * k + 2] = v.z;
@@ -399,7 +400,7 @@ __device__ __forceinline__ void load_link(const LinkPtr &U, int p, int mu, long 
     } else {
         const uint2 *b = static_cast<const uint2 *>(U.d) + base;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) h4_to_f(ldv<true>(b + k * U.Vh + s), t + 4 * k);
+        for (int k = 0; k < 3; ++k) h4_to_f(ldv<NT>(b + k * U.Vh + s), t + 4 * k);
     }
 #pragma unroll
     for (int k = 0; k < 6; ++k) u[k] = cx<R>{t[2 * k], t[2 * k + 1]};

@@ -70,8 +70,6 @@ hipError_t launch_convert_links(const double *links64, void *dst, int prec, Geom
 // clover term A = 1 + T on both parities (structured blocks, FP64)
 hipError_t launch_clover_build(const double *links64, double *clov64, Geom g, double kappa, double csw,
                                hipStream_t st);
-// set the a[3] entries of the even sites' structured FP64 blocks (see load_ct)
-hipError_t launch_clover_check(double *clov64_even, Geom g, hipStream_t st);
 // structured blocks of both parities, FP64 -> FP32 / FP16
 hipError_t launch_convert_ct(const double *src, void *dst, int prec, long Vh, hipStream_t st);
 // structured FP64 blocks of both parities -> general FP16 ones (A = 1 + T rounded)
