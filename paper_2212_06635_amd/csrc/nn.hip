@@ -533,104 +533,149 @@ __global__ void __launch_bounds__(256) nn_layer_kernel(Geom g, Act x, Act y, Spi
 }
 
 // ---------------------------------------------------------------------------
-// weight gradient: P_d[m][k] += sum_n Dl[m][n] Z_d[k][n]   (grid.y = path)
+// weight gradient: P_d[m][k] += sum_n Dl[m][n] Z_d[k][n], all nine paths d
 // ---------------------------------------------------------------------------
-// Tiles of 64 sites; the transported input (staged as in the layer kernel)
-// and the output adjoint are written to LDS with n innermost, the
-// contraction over n runs on v_mfma_f32_16x16x32_bf16.  Sites where one of
-// the two factors vanishes identically (odd-supported input, odd-only output
-// adjoint) are skipped as whole ranges.
+// Two groups of four waves per workgroup, each on its own 64-site tile.  Per
+// tile the output adjoint Dl goes through LDS into registers once and serves
+// all nine paths, whose transported inputs Z_d follow one another through two
+// LDS buffers, the loads of path d + 1 in flight while path d is contracted
+// on v_mfma_f32_16x16x32_bf16 over n = (site, colour); every wave keeps the
+// nine paths' sums of its output tiles in registers (a workgroup per path
+// read and staged Dl nine times and waited for every load: 8 -> 8 at 16^3x32
+// 294 us, now 131 us; 1 -> 8 114 -> 37 us, 8 -> 1 65 -> 49 us).  Bound by LDS
+// traffic (1.1 of 3.6 us a path step) and the latency of the one path ahead.
+// The transport runs with its operands exchanged, D = W Psi, so that lane q of
+// a site receives spin q's three colours, which with a zero fourth are eight
+// consecutive bytes of a row k = (channel, spin, re / im): the LDS rows are
+// written 8 bytes at a time instead of 2.
+// Sites where one of the two factors vanishes identically (odd-supported
+// input, odd-only output adjoint) are skipped as whole ranges.
+constexpr int WG_N = 4 * NN_S;       // contraction length of a tile (fourth colour zero)
+constexpr int WG_STR = WG_N + NN_PAD;  // row stride: 16 rows on different banks
+
+// colours 0..2 of one spin (FP32 re, im) -> BF16 vectors of the re and im parts
+__device__ __forceinline__ void wg_pack(const f32x4 re, const f32x4 im, uint2 &ore, uint2 &oim)
+{
+    ore = make_uint2(f2bf2(re[0], re[1]), f2bf2(re[2], 0.f));
+    oim = make_uint2(f2bf2(im[0], im[1]), f2bf2(im[2], 0.f));
+}
+
 template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) nn_wgrad_kernel(Geom g, Act x, Act dy, NnLinks L, int t_bc, float *partial)
+__global__ void __launch_bounds__(512) nn_wgrad_kernel(Geom g, Act x, Act dy, NnLinks L, int t_bc, float *partial)
 {
     constexpr int KD = pad16(8 * CIN), MD = pad16(8 * COUT);
-    constexpr int NSTR = NN_N + NN_PAD;
-    constexpr int MT = MD / 16, KT = KD / 16, NTILE = MT * KT;
-    constexpr int PER_WAVE = (NTILE + 3) / 4;
-    static_assert(NN_S == NL_S, "one tile size");
-    __shared__ __attribute__((aligned(16))) uint16_t Dl[MD][NSTR];
-    __shared__ __attribute__((aligned(16))) uint16_t Zt[KD][NSTR];
-    const long V = 2L * g.Vh;
-    const int d = blockIdx.y;
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int sl = threadIdx.x / 4, q = threadIdx.x % 4;
-    long sb = 0, se = V;
-    if (COUT == 1) sb = g.Vh;  // the output adjoint lives on odd sites
-    if (CIN == 1) {            // odd-supported input: d = 0 feeds odd sites, hops even ones
-        if (d == 0)
-            sb = g.Vh;
-        else
-            se = g.Vh;
-    }
-    const long ntiles = (se - sb + NN_S - 1) / NN_S;
-    for (int i = threadIdx.x; i < MD * NSTR; i += blockDim.x) Dl[i / NSTR][i % NSTR] = 0;
-    for (int i = threadIdx.x; i < KD * NSTR; i += blockDim.x) Zt[i / NSTR][i % NSTR] = 0;
-    f32x4 acc[PER_WAVE];
+    constexpr int MT = MD / 16, KT = KD / 16;
+    constexpr int TPW = MT == 4 ? KT : 1;  // output tiles per wave: (wave, all kt), or (0, wave)
+    constexpr int ROWS = KD > MD ? KD : MD;
+    static_assert(MT == 4 || (MT == 1 && KT == 4), "eight channels on one side");
+    __shared__ __attribute__((aligned(16))) uint16_t Zs[2][2][ROWS][WG_STR];
+    const int grp = threadIdx.x >> 8, tid = threadIdx.x & 255;
+    const int wave = tid / 64, lane = tid % 64;
+    const int sl = tid / 4, q = tid % 4;
+    const int mt = MT == 4 ? wave : 0;
+    for (int i = threadIdx.x; i < 2 * 2 * ROWS * WG_STR; i += 512) (&Zs[0][0][0][0])[i] = 0;
+    f32x4 acc[NN_P][TPW];
 #pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < NN_P; ++d)
+#pragma unroll
+        for (int j = 0; j < TPW; ++j) acc[d][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int buf = 0;  // the buffer written next; each is read between two barriers after its own
+    __syncthreads();
 
-    for (long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const long site0 = sb + tile * NN_S;
-        __syncthreads();
-        SiteCtx sc;
-        site_ctx(g, site0 + sl, se, sc);
-        Stg<CIN> st;
-        stg_load<CIN>(g, x, L, t_bc, d, CIN == 1, sc, q, st);
-        // output adjoint at the site itself: lane q holds spin q of every channel
-        {
-            const long gs = site0 + sl;
+    // paths D0 .. D0 + NP - 1 over the sites [sb, se)
+    auto run = [&](auto d0c, auto npc, long sb, long se) {
+        constexpr int D0 = decltype(d0c)::value, NP = decltype(npc)::value;
+        const long ntiles = (se - sb + NN_S - 1) / NN_S;
+        for (long t2 = blockIdx.x; 2 * t2 < ntiles; t2 += gridDim.x) {
+            const long gs = sb + (2 * t2 + grp) * NN_S + sl;
+            SiteCtx sc;
+            site_ctx(g, gs, se, sc);
+            W3 dv[COUT];
 #pragma unroll
             for (int c = 0; c < COUT; ++c) {
-                W3 v = {0u, 0u, 0u};
-                if (sc.valid) v = ld3(dy.d + ((long)c * dy.stride + gs) * 12 + 3 * q);
-                const uint32_t w[3] = {v.x, v.y, v.z};
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    Dl[c * 8 + 2 * q][sl * 3 + a] = (uint16_t)(w[a] & 0xffffu);
-                    Dl[c * 8 + 2 * q + 1][sl * 3 + a] = (uint16_t)(w[a] >> 16);
-                }
+                dv[c] = W3{0u, 0u, 0u};
+                if (sc.valid) dv[c] = ld3(dy.d + ((long)c * dy.stride + gs) * 12 + 3 * q);
             }
-        }
-        {
-            const Wop w = make_wop(st.ident, st.dag, st.bc, st.w, q);
+            Stg<CIN> st;
+            stg_load<CIN>(g, x, L, t_bc, D0, CIN == 1, sc, q, st);
+            // output adjoint at the site itself: lane q holds spin q of every channel
 #pragma unroll
-            for (int c = 0; c < CIN; ++c) {
-                uint32_t z[4];
-                transport4(w, st.psi[c], z);
-                if (q < 3) {
+            for (int c = 0; c < COUT; ++c) {
+                bf16x4 re, im;
+                split3(dv[c].x, dv[c].y, dv[c].z, re, im);
+                *reinterpret_cast<uint2 *>(&Zs[grp][buf][c * 8 + 2 * q][sl * 4]) = __builtin_bit_cast(uint2, re);
+                *reinterpret_cast<uint2 *>(&Zs[grp][buf][c * 8 + 2 * q + 1][sl * 4]) = __builtin_bit_cast(uint2, im);
+            }
+            __syncthreads();
+            bf16x8 af[WG_N / 32];
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        Zt[c * 8 + 2 * s][sl * 3 + q] = (uint16_t)(z[s] & 0xffffu);
-                        Zt[c * 8 + 2 * s + 1][sl * 3 + q] = (uint16_t)(z[s] >> 16);
+            for (int nk = 0; nk < WG_N / 32; ++nk)
+                af[nk] = *reinterpret_cast<const bf16x8 *>(&Zs[grp][buf][mt * 16 + lane % 16][nk * 32 + 8 * (lane / 16)]);
+            buf ^= 1;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const Wop w = make_wop(st.ident, st.dag, st.bc, st.w, q);
+#pragma unroll
+                for (int c = 0; c < CIN; ++c) {
+                    bf16x4 pre, pim;
+                    split3(st.psi[c].x, st.psi[c].y, st.psi[c].z, pre, pim);
+                    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+                    f32x4 dre = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(w.re, pre, z, 0, 0, 0);
+                    dre = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(w.nim, pim, dre, 0, 0, 0);
+                    f32x4 dim = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(w.im, pre, z, 0, 0, 0);
+                    dim = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(w.re, pim, dim, 0, 0, 0);
+                    uint2 ore, oim;
+                    wg_pack(dre, dim, ore, oim);
+                    *reinterpret_cast<uint2 *>(&Zs[grp][buf][c * 8 + 2 * q][sl * 4]) = ore;
+                    *reinterpret_cast<uint2 *>(&Zs[grp][buf][c * 8 + 2 * q + 1][sl * 4]) = oim;
+                }
+                __syncthreads();
+                if (i + 1 < NP) stg_load<CIN>(g, x, L, t_bc, D0 + i + 1, CIN == 1, sc, q, st);
+#pragma unroll
+                for (int j = 0; j < TPW; ++j) {
+                    const int kt = MT == 4 ? j : wave;
+#pragma unroll
+                    for (int nk = 0; nk < WG_N / 32; ++nk) {
+                        const bf16x8 bz = *reinterpret_cast<const bf16x8 *>(
+                            &Zs[grp][buf][kt * 16 + lane % 16][nk * 32 + 8 * (lane / 16)]);
+                        acc[D0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[nk], bz, acc[D0 + i][j], 0, 0, 0);
                     }
                 }
+                buf ^= 1;
             }
+        }
+    };
+    using std::integral_constant;
+    const long V = 2L * g.Vh;
+    if constexpr (CIN == 1) {  // odd-supported input: d = 0 feeds odd sites, the hops even ones
+        run(integral_constant<int, 0>{}, integral_constant<int, 1>{}, (long)g.Vh, V);
+        run(integral_constant<int, 1>{}, integral_constant<int, NN_P - 1>{}, 0L, (long)g.Vh);
+    } else {  // one output channel: its adjoint lives on odd sites
+        run(integral_constant<int, 0>{}, integral_constant<int, NN_P>{}, COUT == 1 ? (long)g.Vh : 0L, V);
+    }
+
+    // the two groups' sums meet in LDS, path by path
+    float *out = partial + (size_t)blockIdx.x * NN_P * MD * KD;
+    f32x4 *red = reinterpret_cast<f32x4 *>(&Zs[0][0][0][0]);
+#pragma unroll
+    for (int d = 0; d < NN_P; ++d) {
+        __syncthreads();
+        if (grp == 1) {
+#pragma unroll
+            for (int j = 0; j < TPW; ++j) red[j * 256 + tid] = acc[d][j];
         }
         __syncthreads();
+        if (grp == 0) {
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) {
-            const int t = wave + 4 * j;
-            if (t >= NTILE) break;
-            const int mt = t / KT, kt = t % KT;
+            for (int j = 0; j < TPW; ++j) {
+                const f32x4 v = acc[d][j] + red[j * 256 + tid];
+                const int kt = MT == 4 ? j : wave;
 #pragma unroll
-            for (int nk = 0; nk < NN_N / 32; ++nk) {
-                const int nb = nk * 32 + 8 * (lane / 16);
-                const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&Dl[mt * 16 + lane % 16][nb]);
-                const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&Zt[kt * 16 + lane % 16][nb]);
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[j], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) {
+                    const int m = mt * 16 + 4 * (lane / 16) + i, k = kt * 16 + lane % 16;
+                    out[((size_t)d * MD + m) * KD + k] += v[i];
+                }
             }
-        }
-    }
-    float *out = partial + ((size_t)blockIdx.x * NN_P + d) * MD * KD;
-#pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
-        const int t = wave + 4 * j;
-        if (t >= NTILE) break;
-        const int mt = t / KT, kt = t % KT;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = mt * 16 + 4 * (lane / 16) + i, k = kt * 16 + lane % 16;
-            out[m * KD + k] += acc[j][i];
         }
     }
 }
@@ -1088,31 +1133,33 @@ __global__ void __launch_bounds__(256) nn_p1_down_kernel(Geom g, SpinorPtr src, 
 }
 
 // sum of the per-block partials: P[i] = sum_b partial[b][i]
-__global__ void nn_reduce_partials_kernel(const float *partial, int nblocks, int n, float *P)
+// (four waves share 64 elements, each a quarter of the blocks)
+__global__ void __launch_bounds__(256) nn_reduce_partials_kernel(const float *partial, int nblocks, int n, float *P)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    __shared__ float sh[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += partial[(size_t)b * n + i];
-    P[i] = s;
+    if (i < n) {
+#pragma unroll 8
+        for (int b = w; b < nblocks; b += 4) s += partial[(size_t)b * n + i];
+    }
+    sh[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && i < n) P[i] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
 }
 
-// P[l] = sum over blocks of the partials, then the complex weight gradient
+// the complex weight gradient from the summed partials P[d][m][k]:
 //   S[(c,s),(c',s')] = (P00 + P11) + i (P01 - P10)
 //   grad C[c,c'] = 2 conj(sum_{s,s'} S Gamma[s,s']), grad Gamma[s,s'] = 2 conj(sum_{c,c'} S C[c,c'])
-__global__ void nn_grad_combine_kernel(const float *partial, int nblocks, const float *p, float *grad, int cin,
-                                       int cout)
+__global__ void nn_grad_combine_kernel(const float *sum, const float *p, float *grad, int cin, int cout)
 {
     const int MD = pad16(8 * cout), KD = pad16(8 * cin);
     const int per = cin * cout + 16;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= NN_P * per) return;
     const int d = t / per, e = t % per;
-    auto P = [&](int m, int k) {
-        float s = 0.f;
-        for (int b = 0; b < nblocks; ++b) s += partial[((size_t)b * NN_P + d) * MD * KD + m * KD + k];
-        return s;
-    };
+    auto P = [&](int m, int k) { return sum[((size_t)d * MD + m) * KD + k]; };
     auto S = [&](int c, int s, int cp, int sp, float &re, float &im) {
         const int m = c * 8 + s * 2, k = cp * 8 + sp * 2;
         const float p00 = P(m, k), p11 = P(m + 1, k + 1), p01 = P(m, k + 1), p10 = P(m + 1, k);
@@ -1123,7 +1170,9 @@ __global__ void nn_grad_combine_kernel(const float *partial, int nblocks, const 
     float gr = 0.f, gi = 0.f;
     if (e < cin * cout) {
         const int c = e / cin, cp = e % cin;
+#pragma unroll
         for (int s = 0; s < 4; ++s)
+#pragma unroll
             for (int sp = 0; sp < 4; ++sp) {
                 float sr, si;
                 S(c, s, cp, sp, sr, si);
@@ -1134,6 +1183,7 @@ __global__ void nn_grad_combine_kernel(const float *partial, int nblocks, const 
     } else {
         const int s = (e - cin * cout) / 4, sp = (e - cin * cout) % 4;
         for (int c = 0; c < cout; ++c)
+#pragma unroll 8
             for (int cp = 0; cp < cin; ++cp) {
                 float sr, si;
                 S(c, s, cp, sp, sr, si);
@@ -1347,14 +1397,16 @@ int launch_down(tmx_ctx *c, Act x, SpinorPtr yo, const ThinW *W)
     return hip_err(c, hipGetLastError(), "network last layer");
 }
 
-constexpr int WG_BLOCKS = 64;
+// workgroups of the weight gradient (each adds its sums into a partial of its
+// own): one per CU where there is room for their partials, else 64
+constexpr int WG_BLOCKS = 256, WG_BLOCKS_MIN = 64;
 
-int launch_wgrad(tmx_ctx *c, int cin, int cout, Act x, Act dy, float *partial)
+int launch_wgrad(tmx_ctx *c, int cin, int cout, Act x, Act dy, float *partial, int nblocks)
 {
     NnLinks L;
     int r = nn_links(c, L);
     if (r) return r;
-    const dim3 grid(WG_BLOCKS, NN_P), block(256);
+    const dim3 grid(nblocks), block(512);
     const int tb = c->par.t_bc;
     if (cin == 1 && cout == 8)
         hipLaunchKernelGGL((nn_wgrad_kernel<1, 8>), grid, block, 0, c->stream, c->g, x, dy, L, tb, partial);
@@ -1835,16 +1887,18 @@ int tmx_pc_apply(tmx_ctx *c, double *out, const double *in, int dagger)
 
 // gradient of the loss for a set of pairs (internal helper, also used by the
 // gradient check entry point): accumulates into the partial buffers, returns loss
-static int pc_loss_grad(tmx_ctx *c, const double *b, const double *x, const int *idx, int n, int loss_kind, int op,
-                        double *loss)
+static int pc_loss_grad_blocks(tmx_ctx *c, const double *b, const double *x, const int *idx, int n, int loss_kind,
+                               int op, double *loss, int nblocks)
 {
     PcState &s = *c->pc;
     const long Vh = c->Vh;
     const size_t fb = (size_t)Vh * 24;  // doubles per canonical odd field
     float *partial[NN_L];
     for (int l = 0; l < NN_L; ++l) {
-        const size_t np = (size_t)WG_BLOCKS * NN_P * pad16(8 * NN_COUT[l]) * pad16(8 * NN_CIN[l]);
-        partial[l] = static_cast<float *>(ws_get(c, "nn_partial" + std::to_string(l), np * sizeof(float)));
+        const size_t np = (size_t)nblocks * NN_P * pad16(8 * NN_COUT[l]) * pad16(8 * NN_CIN[l]);
+        const std::string name = "nn_partial" + std::to_string(l);
+        partial[l] = static_cast<float *>(nblocks > WG_BLOCKS_MIN ? ws_spare(c, name + "x", np * sizeof(float))
+                                                                  : ws_get(c, name, np * sizeof(float)));
         if (!partial[l]) return set_err(c, TMX_ENOMEM, "network workspace: out of device memory");
         hipLaunchKernelGGL(nn_zero_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, c->stream, partial[l], np);
     }
@@ -1932,9 +1986,9 @@ static int pc_loss_grad(tmx_ctx *c, const double *b, const double *x, const int 
             // P_1 = L_1^dagger L_1, inputs a0, a1 (layer gradients as below)
             Act d1 = act(c, "d1", 8);
             if (!d1.d) return set_err(c, TMX_ENOMEM, "network workspace: out of device memory");
-            r = launch_wgrad(c, 1, 8, delta, acts[1], partial[0]);                     // L_1^dagger
+            r = launch_wgrad(c, 1, 8, delta, acts[1], partial[0], nblocks);                     // L_1^dagger
             if (!r) r = launch_layer(c, 1, 8, delta, d1, SpinorPtr{}, s.Wf[0]);
-            if (!r) r = launch_wgrad(c, 1, 8, acts[0], d1, partial[0]);                // L_1
+            if (!r) r = launch_wgrad(c, 1, 8, acts[0], d1, partial[0], nblocks);                // L_1
             if (r) return r;
             continue;
         }
@@ -1944,19 +1998,19 @@ static int pc_loss_grad(tmx_ctx *c, const double *b, const double *x, const int 
             // forward use on d with output adjoint x.
             Act d3 = act(c, "d3", 8), d2 = act(c, "d2", 8), d1 = act(c, "d1", 8);
             if (!d3.d || !d2.d || !d1.d) return set_err(c, TMX_ENOMEM, "network workspace: out of device memory");
-            r = launch_wgrad(c, 1, 8, delta, acts[3], partial[0]);                     // L_1^dagger
+            r = launch_wgrad(c, 1, 8, delta, acts[3], partial[0], nblocks);                     // L_1^dagger
             if (!r) r = launch_layer(c, 1, 8, delta, d3, SpinorPtr{}, s.Wf[0]);
-            if (!r) r = launch_wgrad(c, 8, 8, d3, acts[2], partial[1]);                // L_2^dagger
+            if (!r) r = launch_wgrad(c, 8, 8, d3, acts[2], partial[1], nblocks);                // L_2^dagger
             if (!r) r = launch_layer(c, 8, 8, d3, d2, SpinorPtr{}, s.Wf[1]);
-            if (!r) r = launch_wgrad(c, 8, 8, acts[1], d2, partial[1]);                // L_2
+            if (!r) r = launch_wgrad(c, 8, 8, acts[1], d2, partial[1], nblocks);                // L_2
             if (!r) r = launch_layer(c, 8, 8, d2, d1, SpinorPtr{}, s.Wa[1]);
-            if (!r) r = launch_wgrad(c, 1, 8, acts[0], d1, partial[0]);                // L_1
+            if (!r) r = launch_wgrad(c, 1, 8, acts[0], d1, partial[0], nblocks);                // L_1
             if (r) return r;
             continue;
         }
         // backward through the layers
         for (int l = NN_L - 1; l >= 0; --l) {
-            r = launch_wgrad(c, NN_CIN[l], NN_COUT[l], acts[l], delta, partial[l]);
+            r = launch_wgrad(c, NN_CIN[l], NN_COUT[l], acts[l], delta, partial[l], nblocks);
             if (r) return r;
             if (l > 0) {
                 Act nd = act(c, "d" + std::to_string(l), NN_CIN[l]);
@@ -1973,15 +2027,28 @@ static int pc_loss_grad(tmx_ctx *c, const double *b, const double *x, const int 
         const int np = NN_P * pad16(8 * NN_COUT[l]) * pad16(8 * NN_CIN[l]);
         float *P = static_cast<float *>(ws_get(c, "nn_P" + std::to_string(l), (size_t)np * sizeof(float)));
         if (!P) return set_err(c, TMX_ENOMEM, "network workspace: out of device memory");
-        hipLaunchKernelGGL(nn_reduce_partials_kernel, dim3((np + 255) / 256), dim3(256), 0, c->stream, partial[l],
-                           WG_BLOCKS, np, P);
-        hipLaunchKernelGGL(nn_grad_combine_kernel, dim3((nthr + 127) / 128), dim3(128), 0, c->stream, P, 1,
+        hipLaunchKernelGGL(nn_reduce_partials_kernel, dim3((np + 63) / 64), dim3(256), 0, c->stream, partial[l],
+                           nblocks, np, P);
+        hipLaunchKernelGGL(nn_grad_combine_kernel, dim3((nthr + 63) / 64), dim3(64), 0, c->stream, P,
                            s.params + layer_param_offset(l), s.grad + layer_param_offset(l), NN_CIN[l], NN_COUT[l]);
     }
     int r = hip_err(c, hipGetLastError(), "grad combine");
     if (r) return r;
     *loss = L;
     return TMX_OK;
+}
+
+static int pc_loss_grad(tmx_ctx *c, const double *b, const double *x, const int *idx, int n, int loss_kind, int op,
+                        double *loss)
+{
+    // (tiles of 64 sites, two per workgroup at a time)
+    if (c->Vh >= 64 * WG_BLOCKS_MIN && !c->spare_busy) {
+        c->spare_busy = true;
+        const int r = pc_loss_grad_blocks(c, b, x, idx, n, loss_kind, op, loss, WG_BLOCKS);
+        c->spare_busy = false;
+        if (r != TMX_ENOMEM) return r;
+    }
+    return pc_loss_grad_blocks(c, b, x, idx, n, loss_kind, op, loss, WG_BLOCKS_MIN);
 }
 
 int tmx_pc_loss_grad(tmx_ctx *c, const double *b, const double *x, int npairs, int loss_kind, int op, double *loss,
