@@ -488,6 +488,10 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
     b.g5x = g5in;
     b.g5out = g5out;
     int k2mode = MODE_DIAG;
+    if (const NFuse *fu = first ? first : last) {
+        a.stop = b.stop = fu->stop;
+        a.it = b.it = fu->it;
+    }
     if (first && first->nrm) {
         k2mode = MODE_NRM;
         b.nrm = first->nrm;
@@ -750,8 +754,10 @@ int tmx_create(const int dims[4], void *hip_stream, tmx_ctx **out)
     c->red.partials = static_cast<double *>(dev_alloc(c, red_partials_bytes(c)));
     c->red.result = static_cast<double *>(dev_alloc(c, red_result_bytes()));
     if (!c->red.partials || !c->red.result ||
-        hipHostMalloc(&c->host_red, sizeof(double) * MAXR * 4, hipHostMallocCoherent) != hipSuccess) {
+        hipHostMalloc(&c->host_red, sizeof(double) * MAXR * 4, hipHostMallocCoherent) != hipSuccess ||
+        hipHostMalloc(&c->mail, MAIL_BYTES, hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
+        if (c->host_red) (void)hipHostFree(c->host_red);
         dev_free(c, c->red.partials);
         dev_free(c, c->red.result);
         delete c;
@@ -763,6 +769,10 @@ int tmx_create(const int dims[4], void *hip_stream, tmx_ctx **out)
     if (hipHostGetDevicePointer(reinterpret_cast<void **>(&c->red.host), c->host_red, 0) != hipSuccess) {
         (void)hipGetLastError();
         c->red.host = nullptr;
+    }
+    if (hipHostGetDevicePointer(&c->mail_dev, c->mail, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        c->mail_dev = nullptr;
     }
     // device address of the allocation-free operator's scratch on this
     // device (resolved here, at set-up; a failure only disables that entry point)
@@ -802,6 +812,7 @@ int tmx_destroy(tmx_ctx *c)
     dev_free(c, c->red.partials);
     dev_free(c, c->red.result);
     if (c->host_red) (void)hipHostFree(c->host_red);
+    if (c->mail) (void)hipHostFree(c->mail);
     tmx_pc_free(c);
     while (!c->allocs.empty()) dev_free(c, c->allocs.begin()->first);
     delete c;

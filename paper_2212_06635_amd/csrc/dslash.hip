@@ -218,6 +218,7 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
 template <int P, int NF, int MODE, int SPT, bool CT>
 __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
 {
+    if (a.stop && *a.stop < a.it) return;
     const long rg = a.rg;
     const long n = (long)a.g.Vh * rg;
     long u = (long)xcd_block(a.xcd) * blockDim.x + threadIdx.x;
@@ -556,6 +557,7 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
     using R = typename RealOf<P>::type;
     extern __shared__ __align__(16) char split_lds[];
     auto *sh = reinterpret_cast<SplitShared<P, R> *>(split_lds);  // one per flavour
+    if (a.stop && *a.stop < a.it) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long n = (long)a.g.Vh * a.rg;
     const long u0 = (long)xcd_block(a.xcd) * 64 + lane;

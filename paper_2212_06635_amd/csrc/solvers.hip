@@ -228,16 +228,22 @@ static int device_sigma(tmx_ctx *c, const double *sigma, int cols, const double 
     return hip_err(c, hipGetLastError(), "shifts");
 }
 
-// x += a p (do_x) ; p = r + b p (do_p)
+// x += a p (do_x) ; p = r + b p (do_p), coefficients in device memory
 template <int PX, int P> struct OpXp {
     static constexpr int NRED = 0;
     SpinorPtr x, p, r;
     int nf, do_x, do_p;
-    const double *a;  // device
-    double b[MAXR];
+    const double *a, *b;
+    double b0;  // the coefficient of p if b is null (one column)
+    // of an iteration enqueued ahead: nothing if *stop < it, no new direction if *stop == it
+    const int *stop;
+    int it;
     __device__ void operator()(long t, int k, double *) const
     {
-        const double ak = a[k], bk = b[k];
+        const int st_it = stop ? *stop : it + 1;
+        if (st_it < it) return;
+        const bool up_p = do_p && st_it != it;
+        const double ak = a[k], bk = !up_p ? 0.0 : (b ? b[k] : b0);
         for (int f = 0; f < nf; ++f) {
             cd vp[12];
             ld<P>(p, f, t, vp);
@@ -248,7 +254,7 @@ template <int PX, int P> struct OpXp {
                 for (int c = 0; c < 12; ++c) vx[c] = vx[c] + ak * vp[c];
                 st<PX>(x, f, t, vx);
             }
-            if (do_p) {
+            if (up_p) {
                 cd vr[12];
                 ld<P>(r, f, t, vr);
 #pragma unroll
@@ -258,6 +264,125 @@ template <int PX, int P> struct OpXp {
         }
     }
 };
+
+// --------------------------------------------------------------------------
+// CG state on the device: the iteration's scalars and decisions, so that the
+// host can enqueue the next iteration before it has seen this one's residual
+// --------------------------------------------------------------------------
+// Iteration `it` ends a stretch (stop = it) when every column has converged,
+// when a mixed-precision solve needs a reliable update, or on a non-finite
+// residual; what the host has enqueued beyond it then does nothing.
+struct CgState {
+    double rho[MAXR], rmax[MAXR], bb[MAXR], alpha[MAXR], beta[MAXR];
+    int active[MAXR];
+    int stop;
+};
+struct CgMail {  // result of one iteration, written last: seq = it + 1
+    double rho[MAXR];
+    int active[MAXR];
+    int stop, seq;
+};
+constexpr int MAIL_RING = 4;
+static_assert(MAIL_RING * sizeof(CgMail) <= MAIL_BYTES, "mail ring");
+
+struct CgSet {
+    double rho[MAXR], rmax[MAXR], bb[MAXR], beta[MAXR];
+    int active[MAXR];
+};
+static __global__ void cg_set_kernel(CgState *s, CgSet a)
+{
+    const int k = threadIdx.x;
+    if (k < MAXR) {
+        s->rho[k] = a.rho[k];
+        s->rmax[k] = a.rmax[k];
+        s->bb[k] = a.bb[k];
+        s->active[k] = a.active[k];
+        s->alpha[k] = 0.0;
+        s->beta[k] = a.beta[k];
+    }
+    if (k == 0) s->stop = 0x7fffffff;
+}
+
+// alpha of every column (one block each)
+static __global__ void __launch_bounds__(256) cg_step_alpha_kernel(const double *part, int n, CgState *s, int it)
+{
+    if (s->stop < it) return;
+    const int k = blockIdx.x;
+    const double pq = column_sum(part, n, gridDim.x, k);
+    if (threadIdx.x == 0) s->alpha[k] = (s->active[k] && pq != 0.0) ? s->rho[k] / pq : 0.0;
+}
+
+// column sums of |r|^2 into sum (several columns: one block each)
+static __global__ void __launch_bounds__(256) cg_step_sum_kernel(const double *part, int n, const CgState *s, int it,
+                                                                 double *sum)
+{
+    if (s->stop < it) return;
+    const double v = column_sum(part, n, gridDim.x, blockIdx.x);
+    if (threadIdx.x == 0) sum[blockIdx.x] = v;
+}
+
+// the iteration's decisions from |r|^2 (part: the partials of one column, or
+// the sums of several); mixed: reliable updates at a drop of delta
+static __global__ void __launch_bounds__(256) cg_step_end_kernel(const double *part, int n, int cols, CgState *s, int it,
+                                                                 double tol, double delta, int mixed, CgMail *ring)
+{
+    if (s->stop < it) return;
+    __shared__ double r1[MAXR];
+    if (cols == 1) {
+        const double v = column_sum(part, n, 1, 0);
+        if (threadIdx.x == 0) r1[0] = v;
+    } else if ((int)threadIdx.x < cols) {
+        r1[threadIdx.x] = part[threadIdx.x];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    bool stop = false, left = false;
+    for (int k = 0; k < cols; ++k) {
+        if (!s->active[k]) continue;
+        const double v = r1[k];
+        if (!isfinite(v)) stop = true;
+        s->rmax[k] = fmax(s->rmax[k], v);
+        const bool done = sqrt(v) <= tol * sqrt(s->bb[k]);
+        if (mixed && (done || sqrt(v) < delta * sqrt(s->rmax[k]))) stop = true;
+        if (!mixed && done) s->active[k] = 0;
+        left = left || s->active[k];
+    }
+    stop = stop || !left;
+    CgMail &m = ring[it % MAIL_RING];
+    for (int k = 0; k < cols; ++k) {
+        s->beta[k] = s->active[k] ? r1[k] / s->rho[k] : 0.0;
+        s->rho[k] = r1[k];
+        m.rho[k] = r1[k];
+        m.active[k] = s->active[k];
+    }
+    m.stop = stop ? 1 : 0;
+    __threadfence_system();
+    __hip_atomic_store(&m.seq, it + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (stop) s->stop = it;
+}
+
+// wait for the result of iteration it
+static int cg_wait(tmx_ctx *c, int it, const CgMail *dev_ring, CgMail *out)
+{
+    CgMail *ring = static_cast<CgMail *>(c->mail);
+    CgMail &m = ring[it % MAIL_RING];
+    if (!c->mail_dev) {  // not mapped: the kernels write device memory, copied here
+        HTRY(hipMemcpyAsync(&m, dev_ring + it % MAIL_RING, sizeof(CgMail), hipMemcpyDeviceToHost, c->stream),
+             "iteration readback");
+        HTRY(hipStreamSynchronize(c->stream), "iteration readback");
+    }
+    for (long spin = 0; __atomic_load_n(&m.seq, __ATOMIC_ACQUIRE) != it + 1; ++spin) {
+        if (spin % 1024 != 1023) continue;
+        // the stream has drained (or failed) without the result: an error, not a wait
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess) return hip_err(c, e, "iteration readback");
+        if (__atomic_load_n(&m.seq, __ATOMIC_ACQUIRE) != it + 1)
+            return set_err(c, TMX_EHIP, "an iteration's result did not arrive");
+    }
+    *out = m;
+    return TMX_OK;
+}
 
 // preconditioned CG step length alpha = rho / <p, q> on the device (0 for a
 // non-positive <p, q>: breakdown, seen on the host when it reads alpha), also
@@ -340,20 +465,23 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
     SpinorPtr p = S.field("p", P, cols);
     SpinorPtr xl = mixed ? S.field("xl", F32, cols) : x;
     TRY(S.need());
-    double *alpha = static_cast<double *>(ws_get(c, "cg_alpha", sizeof(double) * MAXR));
+    CgState *state = static_cast<CgState *>(ws_get(c, "cg_state", sizeof(CgState)));
     // per-slot |Mhat p|^2 + sigma |p|^2 = <p, (N + sigma) p>, then |r|^2: both
     // written by the operator's own kernels
     double *nrm = static_cast<double *>(ws_get(c, "cg_pnrm", sizeof(double) * c->Vh * cols));
-    if (!alpha || !nrm) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
+    CgMail *ring = static_cast<CgMail *>(c->mail_dev);
+    if (!ring) ring = static_cast<CgMail *>(ws_get(c, "cg_mail", MAIL_RING * sizeof(CgMail)));
+    if (!state || !nrm || !ring) return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
     NFuse fuse{};
     TRY(device_sigma(c, sigma, cols, &fuse.sigma));
     fuse.nsig = fuse.sigma;
     fuse.nrm = fuse.rnrm = nrm;
     fuse.res = true;
     fuse.rin = fuse.rout = rl;
-    fuse.alpha = alpha;
+    fuse.alpha = state->alpha;
+    fuse.stop = &state->stop;
 
-    double bb[MAXR], rho[MAXR], rho1[MAXR], rmax[MAXR], tr[MAXR];
+    double bb[MAXR], rho[MAXR], rho1[MAXR], rmax[MAXR], tr[MAXR], beta[MAXR] = {};
     int active[MAXR], iters[MAXR], nrel[MAXR];
     TRY((copy_field<F64, F64>(S, r, b, cols, bb)));
     for (int k = 0; k < cols; ++k)  // a NaN or infinite entry makes |b|^2 non-finite (x untouched)
@@ -378,74 +506,113 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
         nactive += active[k];
     }
     const double t0 = now_seconds();
-    int it = 0;
-    bool tr_current = true;  // tr holds the true residual of x
-    while (nactive > 0 && it < maxiter) {
-        // an iteration: K1, K2 (writes <p, (N + sigma) p>), alpha, K1, K2
-        // (r -= alpha (N + sigma) p, |r|^2), then x and p in one pass: 12
-        // spinors of vector traffic instead of 15
-        AlphaArgs aa{};
+    // results of an earlier solve are still in the ring (nothing is in flight:
+    // the readback above waited for the stream)
+    for (int i = 0; i < MAIL_RING; ++i) static_cast<CgMail *>(c->mail)[i].seq = 0;
+    // start of a stretch of iterations: scalars to the device
+    auto set_state = [&]() -> int {
+        CgSet a{};
         for (int k = 0; k < cols; ++k) {
-            aa.rho[k] = rho[k];
-            aa.active[k] = active[k];
+            a.rho[k] = rho[k];
+            a.rmax[k] = rmax[k];
+            a.bb[k] = bb[k];
+            a.beta[k] = beta[k];
+            a.active[k] = active[k];
         }
+        hipLaunchKernelGGL(cg_set_kernel, dim3(1), dim3(64), 0, c->stream, state, a);
+        return hip_err(c, hipGetLastError(), "cg state");
+    };
+    OpXp<mixed ? F32 : F64, P> xp{};
+    xp.x = xl;
+    xp.p = p;
+    xp.r = rl;
+    xp.nf = S.nf;
+    xp.a = state->alpha;
+    xp.b = state->beta;
+    // An iteration: K1, K2 (writes <p, (N + sigma) p>), alpha, K1, K2 (r -=
+    // alpha (N + sigma) p, |r|^2), decisions, then x and p in one pass: 12
+    // spinors of vector traffic instead of 15, and no host round trip.
+    auto enqueue = [&](int i) -> int {
+        fuse.it = i;
         fuse.between = [&]() -> int {
             SlotPartials sp;
             TRY(slot_partials(c, nrm, cols, &sp));
-            hipLaunchKernelGGL(cg_alpha_kernel, dim3(cols), dim3(256), 0, c->stream, sp.part, sp.n, aa, alpha,
-                               nullptr);
+            hipLaunchKernelGGL(cg_step_alpha_kernel, dim3(cols), dim3(256), 0, c->stream, sp.part, sp.n, state, i);
             return hip_err(c, hipGetLastError(), "cg step length");
         };
         TRY(S.N(rl, p, P, cols, &fuse));
+        SlotPartials sp;
+        TRY(slot_partials(c, nrm, cols, &sp));
+        if (cols > 1) {
+            hipLaunchKernelGGL(cg_step_sum_kernel, dim3(cols), dim3(256), 0, c->stream, sp.part, sp.n, state, i,
+                               c->red.result);
+            HTRY(hipGetLastError(), "cg residual sums");
+            sp.part = c->red.result;
+        }
+        hipLaunchKernelGGL(cg_step_end_kernel, dim3(1), dim3(256), 0, c->stream, sp.part, sp.n, cols, state, i, tol,
+                           delta, mixed ? 1 : 0, ring);
+        HTRY(hipGetLastError(), "cg iteration");
+        xp.stop = &state->stop;
+        xp.it = i;
+        xp.do_x = xp.do_p = 1;
+        HTRY(run_blas(xp, c->Vh * cols, cols, c->red, c->stream), "cg x, p update");
+        return TMX_OK;
+    };
+    // one iteration is enqueued beyond the one whose result is read: the
+    // round trip (25 us, against 35 us of kernels at 8^4) overlaps it
+    // (not while kernels are timed: a launch that does nothing is no sample)
+    const int ahead = c->mail_dev && !c->kstats_on ? 1 : 0;
+    int it = 0, issued = 0;  // iterations whose result has been read, and enqueued
+    bool tr_current = true;  // tr holds the true residual of x
+    if (nactive > 0) TRY(set_state());
+    while (nactive > 0 && it < maxiter) {
+        while (issued < maxiter && issued <= it + ahead) TRY(enqueue(issued++));
+        CgMail m;
+        TRY(cg_wait(c, it, ring, &m));
         ++it;
         tr_current = false;
-        TRY(fetch_slot_sums(c, nrm, cols, rho1));
-        bool reliable = false;
-        for (int k = 0; k < cols; ++k) {
-            if (!active[k]) continue;
-            iters[k] = it;
-            if (!std::isfinite(rho1[k])) return set_err(c, TMX_ENOCONV, "CG: non-finite residual");
-            rmax[k] = std::max(rmax[k], rho1[k]);
-            if (mixed) {
-                if (std::sqrt(rho1[k]) < delta * std::sqrt(rmax[k]) || std::sqrt(rho1[k]) <= tol * std::sqrt(bb[k]))
-                    reliable = true;
-            }
-        }
-        OpXp<mixed ? F32 : F64, P> xp{};
-        xp.x = xl;
-        xp.p = p;
-        xp.r = rl;
-        xp.nf = S.nf;
-        xp.a = alpha;
-        xp.do_x = 1;
-        if (mixed && reliable) {
-            // x += xl ; xl = 0 ; r = b - N x ; rl = r
-            HTRY(run_blas(xp, c->Vh * cols, cols, c->red, c->stream), "cg x update");
-            xp.do_x = 0;
-            OpAddTo<F64, F32> ad{};
-            ad.x = x;
-            ad.y = xl;
-            ad.nf = S.nf;
-            ad.zero_y = 1;
-            HTRY(run_blas(ad, c->Vh * cols, cols, c->red, c->stream), "reliable add");
-            TRY(true_residual<P>(S, r, rl, true, b, x, sigma, cols, rho1));
-            tr_current = true;
-            for (int k = 0; k < cols; ++k) {
-                tr[k] = rho1[k];
-                if (!active[k]) continue;
-                rmax[k] = rho1[k];
-                nrel[k]++;
-            }
-        }
         nactive = 0;
         for (int k = 0; k < cols; ++k) {
-            if (active[k] && std::sqrt(rho1[k]) <= tol * std::sqrt(bb[k]) && (!mixed || reliable)) active[k] = 0;
-            xp.b[k] = active[k] ? rho1[k] / rho[k] : 0.0;
-            nactive += active[k];
-            rho[k] = rho1[k];
+            rho1[k] = m.rho[k];
+            if (active[k]) {
+                iters[k] = it;
+                if (!std::isfinite(rho1[k])) return set_err(c, TMX_ENOCONV, "CG: non-finite residual");
+                rmax[k] = std::max(rmax[k], rho1[k]);
+                active[k] = m.active[k];
+                nactive += active[k];
+            }
+            if (!m.stop) rho[k] = rho1[k];
         }
-        xp.do_p = nactive > 0;
-        if (xp.do_x || xp.do_p) HTRY(run_blas(xp, c->Vh * cols, cols, c->red, c->stream), "cg x, p update");
+        if (!m.stop) continue;
+        S.gbytes -= (issued - it) * 2.0 * mhat_bytes_per_site(P, S.nf, cols) * c->Vh * 1e-9;
+        issued = it;        // what was enqueued beyond does nothing
+        if (!mixed) break;  // every column has converged
+        // reliable update: x += xl ; xl = 0 ; r = b - N x ; rl = r ; p = rl + beta p
+        OpAddTo<F64, F32> ad{};
+        ad.x = x;
+        ad.y = xl;
+        ad.nf = S.nf;
+        ad.zero_y = 1;
+        HTRY(run_blas(ad, c->Vh * cols, cols, c->red, c->stream), "reliable add");
+        TRY(true_residual<P>(S, r, rl, true, b, x, sigma, cols, tr));
+        tr_current = true;
+        nactive = 0;
+        for (int k = 0; k < cols; ++k) {
+            if (active[k]) {
+                rmax[k] = tr[k];
+                nrel[k]++;
+                if (std::sqrt(tr[k]) <= tol * std::sqrt(bb[k])) active[k] = 0;
+            }
+            beta[k] = active[k] ? tr[k] / rho[k] : 0.0;
+            rho[k] = tr[k];
+            nactive += active[k];
+        }
+        if (nactive == 0) break;
+        TRY(set_state());
+        xp.stop = nullptr;
+        xp.do_x = 0;
+        xp.do_p = 1;
+        HTRY(run_blas(xp, c->Vh * cols, cols, c->red, c->stream), "cg p update");
     }
     if (mixed && nactive > 0) {
         // iteration cap reached mid-way: fold the low-precision increment in
@@ -919,7 +1086,7 @@ static int mscg_core(Sys &S, const std::vector<SpinorPtr> &xs, const std::vector
             xp.r = r;
             xp.nf = S.nf;
             xp.a = alpha;
-            xp.b[0] = bt;
+            xp.b0 = bt;
             xp.do_x = 1;
             xp.do_p = 1;
             HTRY(run_blas(xp, c->Vh, 1, c->red, c->stream), "ms x_0, p_0 update");
@@ -1124,7 +1291,9 @@ static int reserve_cg(Sys &S, int prec)
     (void)S.field("r", F64, 1), (void)S.field("rl", prec, 1), (void)S.field("p", prec, 1), (void)S.field("xl", F32, 1);
     (void)S.field("msx64", F64, 1);
     TRY(S.need());
-    if (!ws_get(c, "cg_alpha", sizeof(double) * MAXR) || !ws_get(c, "cg_pnrm", sizeof(double) * c->Vh))
+    if (!ws_get(c, "cg_alpha", sizeof(double) * MAXR) || !ws_get(c, "cg_pnrm", sizeof(double) * c->Vh) ||
+        !ws_get(c, "cg_state", sizeof(CgState)) ||
+        (!c->mail_dev && !ws_get(c, "cg_mail", MAIL_RING * sizeof(CgMail))))
         return set_err(c, TMX_ENOMEM, "solver workspace: out of device memory");
     TRY(reserve_operator(S, F64));
     return reserve_operator(S, prec);

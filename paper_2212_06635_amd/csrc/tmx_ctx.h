@@ -55,6 +55,8 @@ struct LaunchCfg {
     int rg = 0;
 };
 
+constexpr size_t MAIL_BYTES = 4096;
+
 // block slot after the three precisions: FP16 blocks holding A itself
 constexpr int F16A = 3;
 
@@ -103,6 +105,9 @@ struct tmx_ctx {
     // reductions
     tmx::RedWork red{};
     double *host_red = nullptr;  // pinned
+    // iteration results of the solvers that run ahead of the host: pinned
+    // ring, and its device view (null if it is not mapped)
+    void *mail = nullptr, *mail_dev = nullptr;
 
     // named scratch buffers
     std::map<std::string, tmx::Workspace> ws;
@@ -186,6 +191,8 @@ struct NFuse {
     int lo = 0;
     const double *alpha = nullptr, *sigma = nullptr;
     double *rnrm = nullptr;
+    const int *stop = nullptr;  // the kernels do nothing if *stop < it (see DslashArgs)
+    int it = 0;
     std::function<int()> between;  // called once nrm is enqueued (to enqueue alpha)
 };
 // out = N in = Mhat^dagger Mhat in

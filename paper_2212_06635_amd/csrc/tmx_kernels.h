@@ -39,6 +39,9 @@ struct DslashArgs {
     SpinorPtr rin, rout, rp, rlo;
     int rlo_prec;
     const double *ralpha, *rsig;
+    // of an iteration a solver has enqueued ahead: nothing runs if *stop < it
+    const int *stop;
+    int it;
     double rho;        // MODE_DIAG, one flavour: adds i rho x to the final output (after g5out)
     int r0, rg;        // right-hand sides r0 .. r0 + rg - 1 of the nrhs per site (rg = 0: all)
     int spt;           // sites (slots) per thread: 1, or a grid-stride loop over spt of them
