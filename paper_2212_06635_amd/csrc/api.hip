@@ -1107,13 +1107,8 @@ static int force_fields_internal(tmx_ctx *c, SpinorPtr X, SpinorPtr Y, int op, F
     a.sgn = sgn;
     a.in = ff.X;
     a.out = ff.u;
-    hipError_t e = launch_dslash(F64, nf, k1mode, a, c->stream, l1.block);
-    if (e != hipSuccess) return hip_err(c, e, "K1 launch");
-    a.sgn = -sgn;
-    a.g5in = 1;
-    a.in = ff.Y;
-    a.out = ff.w;
-    e = launch_dslash(F64, nf, k1mode, a, c->stream, l1.block);
+    // w takes -sgn and g5 on its input
+    const hipError_t e = launch_dslash_pair(nf, k1mode, a, ff.Y, ff.w, c->stream, l1.block);
     return e != hipSuccess ? hip_err(c, e, "K1 launch") : TMX_OK;
 }
 

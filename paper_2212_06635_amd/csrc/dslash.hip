@@ -154,7 +154,7 @@ __device__ __forceinline__ void load_spinor_g5(const SpinorPtr &f, int flav, lon
 }
 
 // accumulate (H in)(s) for all flavours
-template <int P, int NF, int MU, typename R>
+template <int P, int NF, int MU, bool NT, typename R>
 __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int s, long rhs, cx<R> acc[NF][12])
 {
     const Geom &g = a.g;
@@ -169,7 +169,7 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int
         }
         const int n = cb_index(g, y);
         cx<R> u[9];
-        load_link<P>(a.U, p, MU, s, u);
+        load_link<P, NT>(a.U, p, MU, s, u);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             cx<R> psi[12];
@@ -196,7 +196,7 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int
         }
         const int n = cb_index(g, y);
         cx<R> u[9];
-        load_link<P>(a.U, 1 - p, MU, n, u);
+        load_link<P, NT>(a.U, 1 - p, MU, n, u);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             cx<R> psi[12];
@@ -208,7 +208,7 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int
     }
 }
 
-template <int P, int NF, int MODE, bool CT>
+template <int P, int NF, int MODE, bool CT, bool NT = true>
 __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs);
 
 // Thread i takes the work items i, i + G, ..., i + (SPT - 1) G (G the grid's
@@ -235,6 +235,29 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
     }
 }
 
+// Two first halves at once, for the force terms: out = B^{-1}(sgn) (H in) and
+// out2 = B^{-1}(-sgn) (H in2) with the other setting of g5in.  Workgroups
+// 2i and 2i + 1 (with the XCD order, on one XCD at about the same time) take
+// the same sites, so links and site blocks, two thirds of the bytes, come
+// from HBM once; they are therefore read through the caches, not past them.
+// FP64 at 32^3x64, the pair: 663 us as two launches, 633 with streamed links,
+// 572 with cached ones (the waves of the pair in one workgroup: 584); 2.0 GB
+// at that size, so waits at two waves per SIMD are what is left.
+template <int NF, int MODE, bool CT>
+__global__ void __launch_bounds__(256) dslash_pair_kernel(DslashArgs a, SpinorPtr in2, SpinorPtr out2)
+{
+    const int blk = xcd_block(a.xcd);
+    const long s = (long)(blk >> 1) * blockDim.x + threadIdx.x;
+    if (s >= a.g.Vh) return;
+    if (blk & 1) {
+        a.in = in2;
+        a.out = out2;
+        a.sgn = -a.sgn;
+        a.g5in = !a.g5in;
+    }
+    dslash_slot<F64, NF, MODE, CT, false>(a, (int)s, 0);
+}
+
 template <typename R> __device__ __forceinline__ void add_norm(double &n2, const cx<R> v[6])
 {
 #pragma unroll
@@ -257,8 +280,9 @@ __device__ __forceinline__ void apply_clov(const void *clov, long cs, long s, in
     }
 }
 
-// one output slot: site s (of the output parity), right-hand side rhs
-template <int P, int NF, int MODE, bool CT>
+// one output slot: site s (of the output parity), right-hand side rhs; NT:
+// links streamed past the caches
+template <int P, int NF, int MODE, bool CT, bool NT>
 __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs)
 {
     using R = typename RealOf<P>::type;
@@ -277,10 +301,10 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
     // occupancy to one wave per SIMD.  t first: its neighbours are the
     // farthest in memory (most often past L2), so their loads go out first
     // (FP64 K1 1.4 % faster than x first)
-    hop_dir<P, NF, 3>(a, x, s, rhs, acc);
-    hop_dir<P, NF, 2>(a, x, s, rhs, acc);
-    hop_dir<P, NF, 1>(a, x, s, rhs, acc);
-    hop_dir<P, NF, 0>(a, x, s, rhs, acc);
+    hop_dir<P, NF, 3, NT>(a, x, s, rhs, acc);
+    hop_dir<P, NF, 2, NT>(a, x, s, rhs, acc);
+    hop_dir<P, NF, 1, NT>(a, x, s, rhs, acc);
+    hop_dir<P, NF, 0, NT>(a, x, s, rhs, acc);
 
     const long cs = a.g.Vh;  // clover stride
     // site-block epilogue, one chirality block at a time (register fences
@@ -755,6 +779,15 @@ static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
     return hipGetLastError();
 }
 
+template <int NF, int MODE, bool CT>
+static hipError_t launch_pair(const DslashArgs &a, const SpinorPtr &in2, const SpinorPtr &out2, hipStream_t st,
+                              int block)
+{
+    const long grid = 2 * ((long)(a.g.Vh + block - 1) / block);
+    hipLaunchKernelGGL((dslash_pair_kernel<NF, MODE, CT>), dim3((unsigned)grid), dim3(block), 0, st, a, in2, out2);
+    return hipGetLastError();
+}
+
 template <int P, int NF>
 static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int block)
 {
@@ -791,6 +824,31 @@ hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a0, hipSt
     if (prec == F32) return nf == 1 ? launch_mode<F32, 1>(mode, a, st, block) : launch_mode<F32, 2>(mode, a, st, block);
     if (prec == F16) return nf == 1 ? launch_mode<F16, 1>(mode, a, st, block) : launch_mode<F16, 2>(mode, a, st, block);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_dslash_pair(int nf, int mode, const DslashArgs &a0, SpinorPtr in2, SpinorPtr out2, hipStream_t st,
+                              int block)
+{
+    if (block <= 0) block = 256;
+    DslashArgs a = a0;
+    a.spt = 1;
+    a.r0 = 0;
+    a.rg = 1;
+    const bool inv = mode == MODE_INV;
+    if (a.nrhs != 1 || (!inv && (mode != MODE_SOLVE || nf != 1 || !a.ct))) return hipErrorInvalidValue;
+    if (a.g.Vh == 0) return hipSuccess;
+    if (nf == 1 ? use_split<F64, 1>(a.g.Vh) : use_split<F64, 2>(a.g.Vh)) {
+        hipError_t e = launch_dslash(F64, nf, mode, a, st, block);
+        if (e != hipSuccess) return e;
+        a.in = in2;
+        a.out = out2;
+        a.sgn = -a.sgn;
+        a.g5in = !a.g5in;
+        return launch_dslash(F64, nf, mode, a, st, block);
+    }
+    if (!inv) return launch_pair<1, MODE_SOLVE, true>(a, in2, out2, st, block);
+    if (nf == 1) return launch_pair<1, MODE_INV, false>(a, in2, out2, st, block);
+    return a.ct ? launch_pair<2, MODE_INV, true>(a, in2, out2, st, block) : launch_pair<2, MODE_INV, false>(a, in2, out2, st, block);
 }
 
 }  // namespace tmx

@@ -48,6 +48,10 @@ struct DslashArgs {
 };
 
 hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a, hipStream_t st, int block);
+// the FP64 first half twice, one right-hand side each: out = B^{-1}(sgn) (H in) as
+// a says, and out2 = B^{-1}(-sgn) (H in2) with the other setting of g5in
+hipError_t launch_dslash_pair(int nf, int mode, const DslashArgs &a, SpinorPtr in2, SpinorPtr out2, hipStream_t st,
+                              int block);
 
 // hopping-term force (force.hip): out[lex][mu] (3x3 complex, canonical link
 // layout) = coeff TA(Q_mu(x)) (+ out if accumulate); X, Y odd, u = K1(s) X,
