@@ -274,7 +274,27 @@ static int ensure_clover(tmx_ctx *c, int slot)
 // right-hand sides the threads of a site share the stored inverse's cache
 // lines (144 / nrhs reals a slot), and repeating the elimination of some 900
 // multiply-adds for each of them would cost more than the bytes it saves.
-static bool can_solve(const tmx_ctx *c, int slot, bool nd) { return !nd && clover_ct(c, slot); }
+// Two flavours: A^2 + nubar^2 - epsbar^2 splits into two Hermitian factors
+// A +- del where nubar <= epsbar.  The two eliminations then replace the
+// stored inverse's 72 of K1's 196 reals a site (structured blocks), but the
+// FP64 kernel runs one wave per SIMD and cannot hide them: N in us, stored ->
+// solved, FP64 / FP32
+//    65536 sites  173 -> 184 / 85 -> 84
+//   331776 sites  717 -> 675 / 343 -> 326
+//  1048576 sites 2129 -> 2037 / 980 -> 907
+// hence the line; FP16 (a solver's inner operator, 216 VGPRs instead of 123)
+// is slower at every size: a solve at 331776 sites 32.5 -> 34.7 ms.
+constexpr int ND_SOLVE_SITES = 98304;
+static double nd_square(const tmx_ctx *c)
+{
+    const double nb = 2.0 * c->par.kappa * c->par.mubar, ep = 2.0 * c->par.kappa * c->par.epsbar;
+    return nb * nb - ep * ep;
+}
+static bool can_solve(const tmx_ctx *c, int slot, bool nd)
+{
+    if (!clover_ct(c, slot)) return false;
+    return !nd || (slot != F16 && c->Vh > ND_SOLVE_SITES && nd_square(c) <= 0.0);
+}
 
 static int ensure_inv(tmx_ctx *c, int prec)
 {
@@ -307,18 +327,26 @@ static int ensure_inv(tmx_ctx *c, int prec)
     return TMX_OK;
 }
 
+// the buffers alone: parameters set later may need the inverse in a call that
+// must not allocate
+static int invnd_buffers(tmx_ctx *c, int prec)
+{
+    for (int p : {(int)F64, prec}) {
+        if (!c->invnd[p]) c->invnd[p] = dev_alloc(c, invnd_bytes(p, c->Vh));
+        if (!c->invnd[p]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
+    }
+    return TMX_OK;
+}
+
 static int ensure_invnd(tmx_ctx *c, int prec)
 {
     int r = ensure_clover(c, F64);
+    if (!r) r = invnd_buffers(c, prec);
     if (r) return r;
     const double nb = 2.0 * c->par.kappa * c->par.mubar, ep = 2.0 * c->par.kappa * c->par.epsbar;
-    const double cc = nb * nb - ep * ep;
+    const double cc = nd_square(c);
     if (c->invnd_ok[F64] && c->invnd_c != cc) c->invnd_ok[0] = c->invnd_ok[1] = c->invnd_ok[2] = false;
     if (!c->invnd_ok[F64]) {
-        if (!c->invnd[F64]) {
-            c->invnd[F64] = dev_alloc(c, invnd_bytes(F64, c->Vh));
-            if (!c->invnd[F64]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
         r = hip_err(c, launch_clover_inv_nd((const double *)c->clov[F64], clover_ct(c, F64), (double *)c->invnd[F64],
                                             c->g, nb, ep, c->stream),
                     "nd clover inverse");
@@ -328,10 +356,6 @@ static int ensure_invnd(tmx_ctx *c, int prec)
         c->invnd_ok[F32] = c->invnd_ok[F16] = false;
     }
     if (prec != F64 && !c->invnd_ok[prec]) {
-        if (!c->invnd[prec]) {
-            c->invnd[prec] = dev_alloc(c, invnd_bytes(prec, c->Vh));
-            if (!c->invnd[prec]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
         r = hip_err(c, launch_convert_seq((const double *)c->invnd[F64], c->invnd[prec], prec, 72, c->Vh, c->stream),
                     "convert nd inverse");
         if (r) return r;
@@ -346,8 +370,11 @@ int ensure_ready(tmx_ctx *c, int prec, bool nd, int nrhs, bool inner)
     const int slot = clover_slot(c, prec, inner);
     int r = ensure_links(c, prec);
     if (!r) r = ensure_clover(c, slot);
-    if (r || (nrhs == 1 && can_solve(c, slot, nd))) return r;
-    return nd ? ensure_invnd(c, prec) : ensure_inv(c, prec);
+    const bool solve = nrhs == 1 && can_solve(c, slot, nd);
+    if (!r && nd) r = solve ? invnd_buffers(c, prec) : ensure_invnd(c, prec);
+    if (!r && !nd && !solve) r = ensure_inv(c, prec);
+    if (!r && !nd) c->ready1[F64] = c->ready1[prec] = true;
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -366,6 +393,7 @@ static int k1_blocks(tmx_ctx *c, DslashArgs &a, int prec, bool nd, int nrhs, boo
     a.clov = clov_parity(c, slot, 0);
     a.ct = clover_ct(c, slot);
     a.inv = nd ? c->invnd[prec] : c->inv[prec];
+    a.del = nd ? std::sqrt(std::max(0.0, -nd_square(c))) : 0.0;
     const bool stored = nd ? c->invnd_ok[prec] : c->inv_ok[prec];
     return can_solve(c, slot, nd) && (nrhs == 1 || !stored) ? MODE_SOLVE : MODE_INV;
 }
@@ -541,17 +569,18 @@ static int op_sign(int op) { return op == TMX_OP_ND ? 1 : (op > 0 ? 1 : -1); }
 static double w_rho(const tmx_ctx *c, int s) { return s * 2.0 * c->par.kappa * c->par.rho; }
 
 // Mhat (or its adjoint) with the even-site intermediate in u (derived fields ready)
-static int mhat_with(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int op, int prec, int dagger, int nrhs)
+static int mhat_with(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int op, int prec, int dagger, int nrhs,
+                     bool inner = false)
 {
     const bool nd = op == TMX_OP_ND;
     const int sgn = op_sign(op);
     if (op_is_w(op)) {
         // What^s = g5 Mhat(s) + i s rho~ ; its adjoint is What^-s
         const int s = dagger ? -sgn : sgn;
-        return schur_pair(c, out, in, u, prec, false, nrhs, s, 0, 1, w_rho(c, s));
+        return schur_pair(c, out, in, u, prec, false, nrhs, s, 0, 1, w_rho(c, s), inner);
     }
     // Mhat^dagger = g5 Mhat(-sgn) g5
-    return schur_pair(c, out, in, u, prec, nd, nrhs, dagger ? -sgn : sgn, dagger, dagger);
+    return schur_pair(c, out, in, u, prec, nd, nrhs, dagger ? -sgn : sgn, dagger, dagger, 0.0, inner);
 }
 
 int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagger, int nrhs)
@@ -1036,19 +1065,22 @@ int tmx_apply_mhat_noalloc(tmx_ctx *c, void *out, const void *in, int op, int pr
                                           "-byte scratch (use tmx_apply_mhat)");
     // every derived field of this precision must exist already (building one
     // would allocate); rebuilding an existing one after new parameters does not
-    const int slot = clover_slot(c, prec, false);
-    const bool have = c->gauge_loaded && c->have_params && c->links[prec] && c->clov[F64] && c->clov[slot];
+    // (FP16 blocks only a solver has prepared are the structured ones of its
+    // iterations)
+    const bool inner = clover_slot(c, prec, false) == F16A && !c->clov[F16A];
+    const int slot = clover_slot(c, prec, inner);
     const bool inv = nd ? (c->invnd[F64] && c->invnd[prec]) : (c->inv[F64] && c->inv[prec]);
-    if (!have || (!inv && !can_solve(c, slot, nd)))
+    const bool have = c->gauge_loaded && c->have_params && c->links[prec] && c->clov[F64] && c->clov[slot];
+    if (!have || !(nd ? inv : c->ready1[prec]) || (!inv && !can_solve(c, slot, nd)))
         return set_err(c, TMX_ENOTLOADED, "tmx_apply_mhat_noalloc: the fields of this precision are not resident "
                                           "(one tmx_apply_mhat in this precision and sector builds them)");
     // without a resident inverse the blocks are inverted in the kernel for any nrhs
-    r = ensure_ready(c, prec, nd, inv ? nrhs : 1);
+    r = ensure_ready(c, prec, nd, inv ? nrhs : 1, inner);
     if (r) return r;
     void *u = scratch_address(c);
     if (!u) return TMX_EHIP;
     const SpinorPtr O = make_spinor(out, prec, nf, stride), I = make_spinor(const_cast<void *>(in), prec, nf, stride);
-    return mhat_with(c, O, I, make_spinor(u, prec, nf, stride), op, prec, dagger ? 1 : 0, nrhs);
+    return mhat_with(c, O, I, make_spinor(u, prec, nf, stride), op, prec, dagger ? 1 : 0, nrhs, inner);
 }
 
 int tmx_apply_mdagm(tmx_ctx *c, void *out, const void *in, int op, int prec, int nrhs)

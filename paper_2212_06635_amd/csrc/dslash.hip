@@ -17,13 +17,16 @@
 //       in FP64: saves the pass that wrote the operator's result and the one
 //       that read it back with r (3 of the 15 spinors of vector traffic in a
 //       CG iteration).
-//   MODE_SOLVE (K1 with the site block inverted in the kernel, one flavour):
+//   MODE_SOLVE (K1 with the site block inverted in the kernel):
 //       out = B_p^{-1}(sgn) (H in)(s) by elimination on the stored A itself.
 //       The stencils are bound by HBM bytes (a wave spends some 130k cycles
 //       mostly waiting, against about 4k for the two eliminations), so 56
 //       reals of site data instead of the inverse's 144 is what counts: with
 //       the structured A in K2 (56 instead of 72) the FP64 Mhat at 32^3x64
 //       went from 772 to 633 us, the FP16 MP-CG from 66.1 to 58.9 ms.
+//       Two flavours (many sites, nubar <= epst): two Hermitian eliminations,
+//       A -+ del, on the one A instead of A and the stored inverse factor;
+//       FP32 Mhat at 24^3x48 177 -> 167 us, FP64 N 717 -> 675 us.
 //   MODE_DIAG (second half, "K2", or one parity of the full operator D):
 //       out = (A_p + X(sgn)) x(s) - kfac (H in)(s)
 //     with X = i sgn nu g5 (degenerate) or the two-flavour X above; for the
@@ -312,15 +315,22 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
     cx<R> out[NF][12];
     double xn2 = 0.0;  // MODE_NRM with nsig: |x|^2
     if constexpr (MODE == MODE_SOLVE) {
-        static_assert(CT && NF == 1, "the in-kernel solve takes structured blocks of one flavour");
+        static_assert(CT, "the in-kernel solve takes structured blocks");
         const R nb = R(a.sgn * a.nu);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             R b[28];
             load_ct<P>(a.clov, cs, s, c, b);
+            const R tw = c == 0 ? nb : -nb;
+            if constexpr (NF == 1) {
 #pragma unroll
-            for (int k = 0; k < 6; ++k) out[0][6 * c + k] = acc[0][6 * c + k];
-            ct_solve(b, c == 0 ? nb : -nb, out[0] + 6 * c);
+                for (int k = 0; k < 6; ++k) out[0][6 * c + k] = acc[0][6 * c + k];
+                ct_solve(b, tw, out[0] + 6 * c);
+            } else {
+                ct_inverse_nd(b, R(a.del), tw, R(a.epst), acc[0] + 6 * c, acc[1] + 6 * c, out[0] + 6 * c,
+                              out[1] + 6 * c);
+                reg_fence(out[1] + 6 * c, 6);
+            }
             reg_fence(out[0] + 6 * c, 6);
         }
     } else if constexpr (MODE == MODE_INV) {
@@ -625,6 +635,7 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
         }
         const R nb = R(a.sgn * a.nu), tw = c == 0 ? nb : -nb, ep = R(a.epst);
         if constexpr (MODE == MODE_SOLVE) {
+            static_assert(NF == 1, "the two-flavour solve is for many sites only");
 #pragma unroll
             for (int k = 0; k < 6; ++k) out[0][k] = acc[0][k];
             ct_solve(b, tw, out[0]);
@@ -767,7 +778,9 @@ template <int P, int NF, int MODE, bool CT>
 static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
 {
     const long n = (long)a.g.Vh * (a.rg > 0 ? a.rg : a.nrhs);
-    if (n > 0 && use_split<P, NF>(n)) return launch_split<P, NF, MODE, CT>(a, st);
+    if constexpr (!(MODE == MODE_SOLVE && NF == 2)) {  // that one is for many sites only
+        if (n > 0 && use_split<P, NF>(n)) return launch_split<P, NF, MODE, CT>(a, st);
+    }
     const long per = block * (long)(a.spt > 0 && MODE != MODE_RES && MODE != MODE_NRM ? a.spt : 1);
     const int grid = (int)((n + per - 1) / per);
     if (n == 0) return hipSuccess;
@@ -792,7 +805,7 @@ template <int P, int NF>
 static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int block)
 {
     if (mode == MODE_SOLVE) {
-        if constexpr (NF == 1)
+        if constexpr (NF == 1 || P != F16)
             return a.ct ? launch_one<P, NF, MODE_SOLVE, true>(a, st, block) : hipErrorInvalidValue;
         else
             return hipErrorInvalidValue;
@@ -835,7 +848,7 @@ hipError_t launch_dslash_pair(int nf, int mode, const DslashArgs &a0, SpinorPtr 
     a.r0 = 0;
     a.rg = 1;
     const bool inv = mode == MODE_INV;
-    if (a.nrhs != 1 || (!inv && (mode != MODE_SOLVE || nf != 1 || !a.ct))) return hipErrorInvalidValue;
+    if (a.nrhs != 1 || (!inv && (mode != MODE_SOLVE || !a.ct))) return hipErrorInvalidValue;
     if (a.g.Vh == 0) return hipSuccess;
     if (nf == 1 ? use_split<F64, 1>(a.g.Vh) : use_split<F64, 2>(a.g.Vh)) {
         hipError_t e = launch_dslash(F64, nf, mode, a, st, block);
@@ -846,7 +859,9 @@ hipError_t launch_dslash_pair(int nf, int mode, const DslashArgs &a0, SpinorPtr 
         a.g5in = !a.g5in;
         return launch_dslash(F64, nf, mode, a, st, block);
     }
-    if (!inv) return launch_pair<1, MODE_SOLVE, true>(a, in2, out2, st, block);
+    if (!inv)
+        return nf == 1 ? launch_pair<1, MODE_SOLVE, true>(a, in2, out2, st, block)
+                       : launch_pair<2, MODE_SOLVE, true>(a, in2, out2, st, block);
     if (nf == 1) return launch_pair<1, MODE_INV, false>(a, in2, out2, st, block);
     return a.ct ? launch_pair<2, MODE_INV, true>(a, in2, out2, st, block) : launch_pair<2, MODE_INV, false>(a, in2, out2, st, block);
 }

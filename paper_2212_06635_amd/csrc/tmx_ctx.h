@@ -95,6 +95,7 @@ struct tmx_ctx {
     // degenerate site inverse (A_ee + i nu g5)^{-1}, per precision
     void *inv[3] = {nullptr, nullptr, nullptr};
     bool inv_ok[3] = {false, false, false};
+    bool ready1[3] = {false, false, false};  // the one-flavour operator of a precision has been prepared once
     double inv_nu = 0;
 
     // two-flavour inverse factor (A_ee^2 + nubar^2 - epst^2)^{-1}

@@ -655,12 +655,12 @@ template <typename R> __device__ __forceinline__ void cmsub(cx<R> &a, cx<R> b, c
 // The same for any block (a[3] = 0): elimination with partial pivoting in
 // FP64.  Rows are indexed at run time, so the matrix lives in scratch; fields
 // rough enough to need it are rare, so only the threads concerned run it.
-template <typename R> __device__ __forceinline__ void ct_solve_pivot(const R a[28], R twist, cx<R> *y)
+template <typename R> __device__ __forceinline__ void ct_solve_pivot(const R a[28], R shift, R twist, cx<R> *y)
 {
     cx<double> m[6][7];
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-        m[i][i] = cx<double>{1.0 + (double)ct_diag(a, i), (double)twist};
+        m[i][i] = cx<double>{1.0 + (double)ct_diag(a, i) + (double)shift, (double)twist};
         m[i][6] = cx<double>{(double)y[i].re, (double)y[i].im};
 #pragma unroll
         for (int j = 0; j < i; ++j) {
@@ -707,7 +707,7 @@ template <typename R> __device__ __forceinline__ void ct_solve_pivot(const R a[2
 template <typename R> __device__ __forceinline__ void ct_solve(const R a[28], R twist, cx<R> *y)
 {
     if (__builtin_expect(a[3] == R(0), 0)) {
-        ct_solve_pivot(a, twist, y);
+        ct_solve_pivot(a, R(0), twist, y);
         return;
     }
     cx<R> m[6][6], p[6];
@@ -738,6 +738,94 @@ template <typename R> __device__ __forceinline__ void ct_solve(const R a[28], R 
 #pragma unroll
         for (int j = k + 1; j < 6; ++j) cmsub(t, m[k][j], y[j]);
         y[k] = t * p[k];
+    }
+}
+
+// 1 + T + shift = L D L^dagger (L unit lower, row i at l[i (i - 1) / 2], d = 1 / D);
+// returns the smallest pivot
+template <typename R> __device__ __forceinline__ R ct_ldl(const R a[28], R shift, cx<R> l[15], R d[6])
+{
+    R g[6], least;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        g[i] = R(1) + ct_diag(a, i) + shift;
+#pragma unroll
+        for (int j = 0; j < i; ++j) l[i * (i - 1) / 2 + j] = ct_lower(a, i, j);
+    }
+    least = g[0];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        least = fmin(least, g[k]);
+        d[k] = R(1) / g[k];
+        cx<R> v[6];  // column k before its division by the pivot
+#pragma unroll
+        for (int i = k + 1; i < 6; ++i) {
+            cx<R> &e = l[i * (i - 1) / 2 + k];
+            v[i] = e;
+            e = d[k] * e;
+#pragma unroll
+            for (int j = k + 1; j < i; ++j) cmsub(l[i * (i - 1) / 2 + j], e, conj(v[j]));
+            g[i] -= e.re * v[i].re + e.im * v[i].im;
+        }
+    }
+    return least;
+}
+
+template <typename R> __device__ __forceinline__ void ct_ldl_solve(const cx<R> l[15], const R d[6], cx<R> *y)
+{
+#pragma unroll
+    for (int k = 1; k < 6; ++k)
+#pragma unroll
+        for (int j = 0; j < k; ++j) cmsub(y[k], l[k * (k - 1) / 2 + j], y[j]);
+#pragma unroll
+    for (int k = 5; k >= 0; --k) {
+        y[k] = d[k] * y[k];
+#pragma unroll
+        for (int j = k + 1; j < 6; ++j) cmsub(y[k], conj(l[j * (j - 1) / 2 + k]), y[j]);
+    }
+}
+
+// out_f = the two-flavour block inverse (A + X)^{-1} of the right-hand sides
+// y_f (overwritten), X = i tw tau3 - ep tau1, for ep^2 - tw^2 = del^2 >= 0:
+// (A - X) (A^2 - del^2)^{-1} by y = (A - del)^{-1} (.), w = (A + del)^{-1} y,
+// A w = y - del w (no product with A).  A + del has at least A's pivots;
+// where those of A - del come out below 1/16, or A's own are not known to be
+// bounded, the thread pivots.
+template <typename R>
+__device__ __forceinline__ void ct_inverse_nd(const R a[28], R del, R tw, R ep, cx<R> *y0, cx<R> *y1, cx<R> *o0,
+                                              cx<R> *o1)
+{
+    cx<R> w0[6], w1[6], l[15];
+    R d[6];
+    const R least = ct_ldl(a, -del, l, d);
+    if (__builtin_expect(a[3] == R(0) || !(least >= R(0.0625)), 0)) {
+        ct_solve_pivot(a, -del, R(0), y0);
+        ct_solve_pivot(a, -del, R(0), y1);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            w0[k] = y0[k];
+            w1[k] = y1[k];
+        }
+        ct_solve_pivot(a, del, R(0), w0);
+        ct_solve_pivot(a, del, R(0), w1);
+    } else {
+        ct_ldl_solve(l, d, y0);
+        ct_ldl_solve(l, d, y1);
+        reg_fence(y0, 6);
+        reg_fence(y1, 6);
+        ct_ldl(a, del, l, d);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            w0[k] = y0[k];
+            w1[k] = y1[k];
+        }
+        ct_ldl_solve(l, d, w0);
+        ct_ldl_solve(l, d, w1);
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        o0[k] = y0[k] - del * w0[k] - tw * imul(w0[k]) + ep * w1[k];
+        o1[k] = y1[k] - del * w1[k] + tw * imul(w1[k]) + ep * w0[k];
     }
 }
 

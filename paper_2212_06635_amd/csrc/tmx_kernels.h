@@ -24,6 +24,7 @@ struct DslashArgs {
     const void *inv;   // MODE_INV: full inverse (deg) or Hermitian inverse factor (nd)
     double nu;         // nu (deg) or nubar (nd), already times 2 kappa
     double epst;       // 2 kappa epsbar (nd)
+    double del;        // MODE_SOLVE (nd): sqrt(epst^2 - nubar^2)
     double kfac;       // MODE_DIAG: coefficient of the hopping term
     int sgn;           // sign of the twist
     int t_bc;          // fermion time boundary factor
