@@ -62,9 +62,10 @@ NAPPLY = 20
 NN_LAYER_FLOPS_PER_SITE = 9 * (8 * 8 * 12 + 4 * 4 * 24) * 8
 NN_LAYER_BYTES_PER_SITE = 384 + 384 + 8 * 36
 
-# algorithmic bytes per output site of one stencil launch (links, blocks and
-# spinors each read once)
-from paper_2212_06635_amd.counters import kernel_bytes_per_site, read_traffic  # noqa: E402
+# the metric's model bytes per output site of one stencil launch (links, general
+# site blocks and spinors each read once), the same for every version of the
+# kernels; launch_bytes_per_site is what a launch on structured blocks moves
+from paper_2212_06635_amd.counters import kernel_bytes_per_site, launch_bytes_per_site, read_traffic  # noqa: E402
 
 PROFILE = os.path.join(ROOT, "profiles", "dslash_schur_32x32x32x64_kernels.txt")
 
@@ -628,7 +629,7 @@ def main():
     stencil = {k: v for k, v in ks.items() if k[:2] in ("K1", "K2") and "_nd" not in k and "_r" not in k}
     dom = max(stencil.items(), key=lambda kv: kv[1][1])
     dname, (dcount, dms) = dom
-    per_launch_bytes = kernel_bytes_per_site(dname) * Vh
+    per_launch_bytes = launch_bytes_per_site(dname) * Vh  # what the launch moves, not the metric's model
     avg_ms = dms / dcount
     achieved = per_launch_bytes / (avg_ms * 1e-3) / 1e9
     # HBM bytes per launch from the committed FETCH_SIZE / WRITE_SIZE summary

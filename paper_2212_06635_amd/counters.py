@@ -29,10 +29,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 STENCIL_SOURCES = ("csrc/dslash.hip", "csrc/tmx_device.h", "csrc/tmx_kernels.h")
 COPY_BYTES = 2 ** 31
 
-# rocprof kernel name -> bench label; dslash_kernel<P, NF, MODE, SPT> (sites per
-# thread: the tuned launch of a kernel uses one of the two)
-LABELS = {f"void tmx::dslash_kernel<{p}, 1, {m}, {t}>(tmx::DslashArgs)": f"K{m + 1}_{n}"
-          for p, n in ((0, "f64"), (1, "f32"), (2, "f16")) for m in (0, 1) for t in (1, 2)}
+# rocprof kernel name -> bench label; dslash_kernel<P, NF, MODE, SPT[, CT]> (sites
+# per thread: the tuned launch of a kernel uses one of the two; CT: structured
+# site blocks; MODE 2 inverts them in the kernel)
+LABELS = {f"void tmx::dslash_kernel<{p}, 1, {m}, {t}{ct}>(tmx::DslashArgs)": f"K{m % 2 + 1}_{n}"
+          for p, n in ((0, "f64"), (1, "f32"), (2, "f16")) for m in (0, 1, 2) for t in (1, 2)
+          for ct in ("", ", false", ", true")}
 
 
 def source_digest() -> str:
@@ -60,6 +62,14 @@ def kernel_bytes_per_site(kernel: str) -> float:
         fixed = 96 * b + 72 * b  # links; Hermitian A_oo
         spin = nf * (72 * b + 3 * norm)  # read hop input and x, write out
     return fixed + nrhs * spin
+
+
+def launch_bytes_per_site(kernel: str) -> float:
+    """Bytes per output site of a one-flavour, one-right-hand-side launch on
+    structured site blocks: 56 reals of A in either half instead of the 144 of
+    the inverse (K1) and the 72 of the general block (K2)."""
+    b = {"f64": 8, "f32": 4, "f16": 2}[kernel.split("_")[1]]
+    return kernel_bytes_per_site(kernel) - (88 if kernel.startswith("K1") else 16) * b
 
 
 def _stats(path):
@@ -125,7 +135,7 @@ def summarize(d: str, vh: int) -> str:
         if kname not in st:
             continue
         calls, avg = st[kname]
-        alg = kernel_bytes_per_site(lab) * vh
+        alg = (launch_bytes_per_site if ", true>" in kname else kernel_bytes_per_site)(lab) * vh
         fe = f[kname] * 1024 * sf
         wr = w[kname] * 1024 * sw
         rd = alg - (24 * {"f64": 8, "f32": 4, "f16": 2}[lab[3:]] + (4 if "f16" in lab else 0)) * vh
