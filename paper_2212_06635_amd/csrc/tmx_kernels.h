@@ -30,6 +30,13 @@ struct DslashArgs {
     int t_bc;          // fermion time boundary factor
     int g5in, g5x, g5out;
     int xcd;           // XCD-aware block order
+    // what every launch reads comes first: its kernel arguments then lie in few cache lines
+    double rho;        // MODE_DIAG, one flavour: adds i rho x to the final output (after g5out)
+    int r0, rg;        // right-hand sides r0 .. r0 + rg - 1 of the nrhs per site (rg = 0: all)
+    int spt;           // sites (slots) per thread: 1, or a grid-stride loop over spt of them
+    // of an iteration a solver has enqueued ahead: nothing runs if *stop < it
+    const int *stop;
+    int it;
     double *nrm;       // MODE_NRM: |out|^2 of every slot (FP64), for <p, N p> = |Mhat p|^2
     const double *nsig;  // MODE_NRM, if set: per right-hand side sigma, adding sigma |x|^2 (<p, (N + sigma) p>)
     // MODE_RES: the result goes into a residual instead of `out`:
@@ -40,12 +47,6 @@ struct DslashArgs {
     SpinorPtr rin, rout, rp, rlo;
     int rlo_prec;
     const double *ralpha, *rsig;
-    // of an iteration a solver has enqueued ahead: nothing runs if *stop < it
-    const int *stop;
-    int it;
-    double rho;        // MODE_DIAG, one flavour: adds i rho x to the final output (after g5out)
-    int r0, rg;        // right-hand sides r0 .. r0 + rg - 1 of the nrhs per site (rg = 0: all)
-    int spt;           // sites (slots) per thread: 1, or a grid-stride loop over spt of them
 };
 
 hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a, hipStream_t st, int block);
