@@ -214,15 +214,20 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int
 template <int P, int NF, int MODE, bool CT, bool NT = true>
 __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs);
 
-// Whether a launch enqueued ahead is not wanted any more.  The empty asm asks
-// for the two arguments together with those of u: their loads go out at once,
-// where a check ahead of everything else made the kernel arguments' miss a
-// serial one more per launch (N at 8^4 in FP64 24.2 -> 23.9 us, in FP16 at
-// 120960 sites 67.4 -> 67.0; the branch itself is still to be waited for,
-// 65.4 without one).
-__device__ __forceinline__ bool stopped(const int *stop, int it, long &u)
+// Whether a launch enqueued ahead is not wanted any more.  Kernel arguments are
+// not loaded ahead of a branch they lie behind, so a check in front of
+// everything made their miss a serial one more per launch; the empty asm asks for
+// those of the check and the first ones the hops need together with those of
+// u.  N in FP64 at 8^4 24.2 -> 22.9 us, in FP16 at 120960 sites 67.4 -> 66.0
+// (65.4 without a check).
+__device__ __forceinline__ bool stopped(const DslashArgs &a, long &u)
 {
-    asm volatile("" : "+v"(u) : "s"(stop), "s"(it));
+    const int *stop = a.stop;
+    const int it = a.it;
+    asm volatile(""
+                 : "+v"(u)
+                 : "s"(stop), "s"(it), "s"(a.in.d), "s"(a.U.d), "s"(a.out.d), "s"(a.clov), "s"(a.parity), "s"(a.nrhs),
+                   "s"(a.t_bc), "s"(a.g5in));
     return stop && *stop < it;
 }
 
@@ -236,7 +241,7 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
     const long rg = a.rg;
     const long n = (long)a.g.Vh * rg;
     long u = (long)xcd_block(a.xcd) * blockDim.x + threadIdx.x;
-    if (stopped(a.stop, a.it, u)) return;
+    if (stopped(a, u)) return;
     if constexpr (SPT == 1) {
         if (u >= n) return;
         const int s = (int)(u / rg);
@@ -606,7 +611,7 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long n = (long)a.g.Vh * a.rg;
     long u0 = (long)xcd_block(a.xcd) * 64 + lane;
-    if (stopped(a.stop, a.it, u0)) return;
+    if (stopped(a, u0)) return;
     const bool live = u0 < n;
     const long u = live ? u0 : n - 1;  // the last workgroup's spare lanes repeat the last slot
     const int s = (int)(u / a.rg);
