@@ -278,12 +278,20 @@ static int ensure_clover(tmx_ctx *c, int slot)
 // A +- del where nubar <= epsbar.  The two eliminations then replace the
 // stored inverse's 72 of K1's 196 reals a site (structured blocks), but the
 // FP64 kernel runs one wave per SIMD and cannot hide them: N in us, stored ->
-// solved, FP64 / FP32
-//    65536 sites  173 -> 184 / 85 -> 84
-//   331776 sites  717 -> 675 / 343 -> 326
-//  1048576 sites 2129 -> 2037 / 980 -> 907
+// solved
+//    65536 sites  173 -> 184
+//   331776 sites  717 -> 675
+//  1048576 sites 2129 -> 2037
 // hence the line; FP16 (a solver's inner operator, 216 VGPRs instead of 123)
 // is slower at every size: a solve at 331776 sites 32.5 -> 34.7 ms.
+// FP32 reads the stored inverse, formed in FP64 and rounded once.  An
+// elimination on blocks rounded to FP32 carries that rounding times the
+// block's condition number, the stored inverse does not: against 64 bits one
+// flavour has 1.2e-7 instead of 7.3e-8 on smooth fields and 2.5e-6 instead of
+// 7e-8 on rough ones (indefinite blocks); two flavours are no worse on smooth
+// fields but 100 times on rough ones.  In FP64 the eliminations' error is the
+// smaller one on every field: the stored inverse goes through A^2 (2.2e-16
+// against 3.2e-16 smooth, 1e-14 against 1e-11 rough).
 constexpr int ND_SOLVE_SITES = 98304;
 static double nd_square(const tmx_ctx *c)
 {
@@ -292,8 +300,8 @@ static double nd_square(const tmx_ctx *c)
 }
 static bool can_solve(const tmx_ctx *c, int slot, bool nd)
 {
-    if (!clover_ct(c, slot)) return false;
-    return !nd || (slot != F16 && c->Vh > ND_SOLVE_SITES && nd_square(c) <= 0.0);
+    if (!clover_ct(c, slot) || slot == F32) return false;
+    return !nd || (slot == F64 && c->Vh > ND_SOLVE_SITES && nd_square(c) <= 0.0);
 }
 
 static int ensure_inv(tmx_ctx *c, int prec)

@@ -24,9 +24,11 @@
 //       reals of site data instead of the inverse's 144 is what counts: with
 //       the structured A in K2 (56 instead of 72) the FP64 Mhat at 32^3x64
 //       went from 772 to 633 us, the FP16 MP-CG from 66.1 to 58.9 ms.
-//       Two flavours (many sites, nubar <= epst): two Hermitian eliminations,
-//       A -+ del, on the one A instead of A and the stored inverse factor;
-//       FP32 Mhat at 24^3x48 177 -> 167 us, FP64 N 717 -> 675 us.
+//       Two flavours (FP64, many sites, nubar <= epst): two Hermitian
+//       eliminations, A -+ del, on the one A instead of A and the stored
+//       inverse factor; N at 24^3x48 717 -> 675 us.
+//       Not in FP32: there the stored inverse, formed in FP64 and rounded
+//       once, is the more accurate one.
 //   MODE_DIAG (second half, "K2", or one parity of the full operator D):
 //       out = (A_p + X(sgn)) x(s) - kfac (H in)(s)
 //     with X = i sgn nu g5 (degenerate) or the two-flavour X above; for the
@@ -822,7 +824,7 @@ template <int P, int NF>
 static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int block)
 {
     if (mode == MODE_SOLVE) {
-        if constexpr (NF == 1 || P != F16)
+        if constexpr (P == F64 || (P == F16 && NF == 1))  // FP32: the stored inverse, formed in FP64
             return a.ct ? launch_one<P, NF, MODE_SOLVE, true>(a, st, block) : hipErrorInvalidValue;
         else
             return hipErrorInvalidValue;
