@@ -14,8 +14,9 @@
 //    (G_1 + i G_2).  A clover term given by the caller is stored as A = 1 + T
 //    in general Hermitian 6x6 blocks.
 //  * site inverses through (A + i nu)^{-1} = (A - i nu)(A^2 + nu^2)^{-1},
-//    with the Hermitian positive A^2 + nu^2 inverted by Cholesky (no
-//    pivoting needed), all in FP64.
+//    with the Hermitian positive A^2 + nu^2 inverted by Cholesky, all in
+//    FP64; where that fails (two flavours: A^2 + nubar^2 - epsbar^2 need not be
+//    positive on rough fields) by elimination with pivoting on its factors.
 #include "tmx_device.h"
 #include "tmx_kernels.h"
 
@@ -480,11 +481,13 @@ hipError_t launch_clover_to_canonical(const double *clov64, int ct, double *cano
 // site inverses
 // ---------------------------------------------------------------------------
 // S^{-1} for Hermitian positive definite 6x6 S via Cholesky S = L L^+:
-// S^{-1} = L^{-+} L^{-1}.
-__device__ void hpd_inverse(const cd S[6][6], cd Sinv[6][6])
+// S^{-1} = L^{-+} L^{-1}.  False (no usable result) where S is not positive, or
+// a pivot has lost half its digits.
+__device__ __forceinline__ bool hpd_inverse(const cd S[6][6], cd Sinv[6][6])
 {
     cd Lm[6][6];
     double dinv[6];
+    bool ok = true;
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
@@ -494,6 +497,7 @@ __device__ void hpd_inverse(const cd S[6][6], cd Sinv[6][6])
         double d = S[j][j].re;
 #pragma unroll
         for (int k = 0; k < j; ++k) d -= Lm[j][k].re * Lm[j][k].re + Lm[j][k].im * Lm[j][k].im;
+        ok = ok && d > 1e-8 * S[j][j].re;
         d = sqrt(d);
         Lm[j][j] = cd{d, 0};
         dinv[j] = 1.0 / d;
@@ -537,6 +541,64 @@ __device__ void hpd_inverse(const cd S[6][6], cd Sinv[6][6])
             for (int k = (i > j ? i : j); k < 6; ++k) cmac_conj(v, W[k][i], W[k][j]);
             Sinv[i][j] = v;
         }
+    return ok;
+}
+
+// (A^2 - z^2)^{-1} = (A - z)^{-1} (A + z)^{-1} for any Hermitian A of the clover
+// field: elimination with partial pivoting, one factor after the other.  Rows
+// are indexed at run time, so the matrix lives in scratch; only fields rough
+// enough to have eigenvalues of A near or below |z| need it.
+__device__ __forceinline__ void inverse_pivot(const double *clov, int ct, long stride, long s, int chir, cd z,
+                                              cd Sinv[6][6])
+{
+    cd m[6][12];
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) m[i][6 + j] = cd{i == j ? 1.0 : 0.0, 0.0};
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+        {
+            cd A[6][6];
+            load_block(clov, ct, stride, s, chir, A);
+            const cd sh = pass == 0 ? z : -z;
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int j = 0; j < 6; ++j) m[i][j] = i == j ? A[i][j] + sh : A[i][j];
+        }
+#pragma unroll 1
+        for (int k = 0; k < 6; ++k) {
+            int r = k;
+            double best = -1.0;
+#pragma unroll 1
+            for (int i = k; i < 6; ++i) {
+                const double n = m[i][k].re * m[i][k].re + m[i][k].im * m[i][k].im;
+                if (n > best) {
+                    best = n;
+                    r = i;
+                }
+            }
+            const cd p{m[r][k].re / best, -m[r][k].im / best};
+#pragma unroll 1
+            for (int j = k; j < 12; ++j) {  // row k = pivot row / pivot
+                const cd t = m[r][j];
+                m[r][j] = m[k][j];
+                m[k][j] = t * p;
+            }
+#pragma unroll 1
+            for (int i = 0; i < 6; ++i) {
+                if (i == k) continue;
+                const cd f = m[i][k];
+#pragma unroll 1
+                for (int j = k; j < 12; ++j) m[i][j] = m[i][j] - f * m[k][j];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) Sinv[i][j] = m[i][6 + j];
 }
 
 // A^2 + c (Hermitian positive for c > -lambda_min(A^2))
@@ -565,7 +627,7 @@ __global__ void __launch_bounds__(64) clover_inv_kernel(const double *clov_even,
     load_block(clov_even, ct, Vh, s, chir, A);
     const double tw = chir == 0 ? nu : -nu;  // i nu gamma5 on this chirality
     herm_square_shift(A, tw * tw, S);
-    hpd_inverse(S, Si);
+    if (!hpd_inverse(S, Si)) inverse_pivot(clov_even, ct, Vh, s, chir, cd{0.0, tw}, Si);
     // (A + i tw)^{-1} = (A - i tw) S^{-1}
     double out[72];
 #pragma unroll
@@ -602,7 +664,8 @@ __global__ void __launch_bounds__(64) clover_inv_nd_kernel(const double *clov_ev
     cd A[6][6], S[6][6], Si[6][6];
     load_block(clov_even, ct, Vh, s, chir, A);
     herm_square_shift(A, c, S);
-    hpd_inverse(S, Si);
+    if (!hpd_inverse(S, Si))
+        inverse_pivot(clov_even, ct, Vh, s, chir, c < 0.0 ? cd{sqrt(-c), 0.0} : cd{0.0, sqrt(c)}, Si);
     store_herm(invnd64, Vh, s, chir, Si);
 }
 
