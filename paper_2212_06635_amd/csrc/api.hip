@@ -218,21 +218,21 @@ static int ensure_links(tmx_ctx *c, int prec)
     return TMX_OK;
 }
 
-// the clover buffer of a slot, large enough for either format: a clover term
-// given by the caller after one built from the links (or the other way round)
-// needs no new buffer
+// the clover buffer of a slot, large enough for every format it may hold: a
+// clover term given by the caller after one built from the links (or the other
+// way round) needs no new buffer
 static int clover_buffer(tmx_ctx *c, int slot)
 {
-    if (!c->clov[slot]) c->clov[slot] = dev_alloc(c, clover_bytes(slot, c->Vh, false));
+    if (!c->clov[slot]) c->clov[slot] = dev_alloc(c, clover_bytes(slot, c->Vh, slot == F16));
     return c->clov[slot] ? TMX_OK : set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
 }
 
 // the block slot an apply reads, and whether it holds structured blocks
 // (clover terms built from the links) or general ones (F16A, and every slot
-// of a clover term given by the caller)
+// of a clover term given by the caller; slot F16 holds structured ones only)
 static int clover_slot(const tmx_ctx *c, int prec, bool inner)
 {
-    return prec == F16 && !inner && !c->clover_from_host ? F16A : prec;
+    return prec == F16 && (!inner || c->clover_from_host) ? F16A : prec;
 }
 static bool clover_ct(const tmx_ctx *c, int slot) { return !c->clover_from_host && slot != F16A; }
 
@@ -259,9 +259,10 @@ static int ensure_clover(tmx_ctx *c, int slot)
         int r = clover_buffer(c, slot);
         if (r) return r;
         const double *src = static_cast<const double *>(c->clov[F64]);
-        r = hip_err(c, ct             ? launch_convert_ct(src, c->clov[slot], slot, c->Vh, c->stream)
-                       : slot == F16A ? launch_convert_ct_general16(src, c->clov[slot], c->Vh, c->stream)
-                                      : launch_convert_seq(src, c->clov[slot], slot, 144, c->Vh, c->stream),
+        const int prec = slot == F16A ? (int)F16 : slot;
+        r = hip_err(c, ct                     ? launch_convert_ct(src, c->clov[slot], prec, c->Vh, c->stream)
+                       : !c->clover_from_host ? launch_convert_ct_general16(src, c->clov[slot], c->Vh, c->stream)
+                                              : launch_convert_seq(src, c->clov[slot], prec, 144, c->Vh, c->stream),
                     "convert clover");
         if (r) return r;
         c->clov_ok[slot] = true;
@@ -304,17 +305,28 @@ static bool can_solve(const tmx_ctx *c, int slot, bool nd)
     return !nd || (slot == F64 && c->Vh > ND_SOLVE_SITES && nd_square(c) <= 0.0);
 }
 
+// Every call that prepares a sector takes the buffers of its inverse, also
+// where the blocks are inverted in the kernel: several right-hand sides, a
+// clover term given later, or new parameters may need the inverse in
+// tmx_apply_mhat_noalloc, which must not allocate.
+static int inverse_buffers(tmx_ctx *c, int prec, bool nd)
+{
+    for (int p : {(int)F64, prec}) {
+        void *&b = nd ? c->invnd[p] : c->inv[p];
+        if (!b) b = dev_alloc(c, nd ? invnd_bytes(p, c->Vh) : inv_bytes(p, c->Vh));
+        if (!b) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
+    }
+    return TMX_OK;
+}
+
 static int ensure_inv(tmx_ctx *c, int prec)
 {
     int r = ensure_clover(c, F64);
+    if (!r) r = inverse_buffers(c, prec, false);
     if (r) return r;
     const double nu = 2.0 * c->par.kappa * c->par.mu;
     if (c->inv_ok[F64] && c->inv_nu != nu) c->inv_ok[0] = c->inv_ok[1] = c->inv_ok[2] = false;
     if (!c->inv_ok[F64]) {
-        if (!c->inv[F64]) {
-            c->inv[F64] = dev_alloc(c, inv_bytes(F64, c->Vh));
-            if (!c->inv[F64]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
         r = hip_err(c, launch_clover_inv((const double *)c->clov[F64], clover_ct(c, F64), (double *)c->inv[F64], c->g, nu, c->stream),
                     "clover inverse");
         if (r) return r;
@@ -323,10 +335,6 @@ static int ensure_inv(tmx_ctx *c, int prec)
         c->inv_ok[F32] = c->inv_ok[F16] = false;
     }
     if (prec != F64 && !c->inv_ok[prec]) {
-        if (!c->inv[prec]) {
-            c->inv[prec] = dev_alloc(c, inv_bytes(prec, c->Vh));
-            if (!c->inv[prec]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-        }
         r = hip_err(c, launch_convert_seq((const double *)c->inv[F64], c->inv[prec], prec, 144, c->Vh, c->stream),
                     "convert inverse");
         if (r) return r;
@@ -335,21 +343,10 @@ static int ensure_inv(tmx_ctx *c, int prec)
     return TMX_OK;
 }
 
-// the buffers alone: parameters set later may need the inverse in a call that
-// must not allocate
-static int invnd_buffers(tmx_ctx *c, int prec)
-{
-    for (int p : {(int)F64, prec}) {
-        if (!c->invnd[p]) c->invnd[p] = dev_alloc(c, invnd_bytes(p, c->Vh));
-        if (!c->invnd[p]) return set_err(c, TMX_ENOMEM, "device buffer: out of device memory");
-    }
-    return TMX_OK;
-}
-
 static int ensure_invnd(tmx_ctx *c, int prec)
 {
     int r = ensure_clover(c, F64);
-    if (!r) r = invnd_buffers(c, prec);
+    if (!r) r = inverse_buffers(c, prec, true);
     if (r) return r;
     const double nb = 2.0 * c->par.kappa * c->par.mubar, ep = 2.0 * c->par.kappa * c->par.epsbar;
     const double cc = nd_square(c);
@@ -378,10 +375,9 @@ int ensure_ready(tmx_ctx *c, int prec, bool nd, int nrhs, bool inner)
     const int slot = clover_slot(c, prec, inner);
     int r = ensure_links(c, prec);
     if (!r) r = ensure_clover(c, slot);
-    const bool solve = nrhs == 1 && can_solve(c, slot, nd);
-    if (!r && nd) r = solve ? invnd_buffers(c, prec) : ensure_invnd(c, prec);
-    if (!r && !nd && !solve) r = ensure_inv(c, prec);
-    if (!r && !nd) c->ready1[F64] = c->ready1[prec] = true;
+    if (!r) r = clover_buffer(c, clover_slot(c, prec, false));  // an application may follow a solve
+    if (!r && nrhs == 1 && can_solve(c, slot, nd)) return inverse_buffers(c, prec, nd);
+    if (!r) r = nd ? ensure_invnd(c, prec) : ensure_inv(c, prec);
     return r;
 }
 
@@ -393,8 +389,8 @@ static const void *clov_parity(tmx_ctx *c, int slot, int parity)
     return static_cast<const char *>(c->clov[slot]) + parity * clover_bytes(slot, c->Vh, clover_ct(c, slot)) / 2;
 }
 
-// site data of a K1 launch and its mode: the stored inverse if it is there and
-// up to date (ensure_ready builds it where it is the faster one), else A itself
+// site data of a K1 launch and its mode (ensure_ready with the same arguments
+// has built what it reads)
 static int k1_blocks(tmx_ctx *c, DslashArgs &a, int prec, bool nd, int nrhs, bool inner)
 {
     const int slot = clover_slot(c, prec, inner);
@@ -402,8 +398,7 @@ static int k1_blocks(tmx_ctx *c, DslashArgs &a, int prec, bool nd, int nrhs, boo
     a.ct = clover_ct(c, slot);
     a.inv = nd ? c->invnd[prec] : c->inv[prec];
     a.del = nd ? std::sqrt(std::max(0.0, -nd_square(c))) : 0.0;
-    const bool stored = nd ? c->invnd_ok[prec] : c->inv_ok[prec];
-    return can_solve(c, slot, nd) && (nrhs == 1 || !stored) ? MODE_SOLVE : MODE_INV;
+    return nrhs == 1 && can_solve(c, slot, nd) ? MODE_SOLVE : MODE_INV;
 }
 
 static void k2_blocks(tmx_ctx *c, DslashArgs &b, int prec, bool inner, int parity = 1)
@@ -577,18 +572,17 @@ static int op_sign(int op) { return op == TMX_OP_ND ? 1 : (op > 0 ? 1 : -1); }
 static double w_rho(const tmx_ctx *c, int s) { return s * 2.0 * c->par.kappa * c->par.rho; }
 
 // Mhat (or its adjoint) with the even-site intermediate in u (derived fields ready)
-static int mhat_with(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int op, int prec, int dagger, int nrhs,
-                     bool inner = false)
+static int mhat_with(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int op, int prec, int dagger, int nrhs)
 {
     const bool nd = op == TMX_OP_ND;
     const int sgn = op_sign(op);
     if (op_is_w(op)) {
         // What^s = g5 Mhat(s) + i s rho~ ; its adjoint is What^-s
         const int s = dagger ? -sgn : sgn;
-        return schur_pair(c, out, in, u, prec, false, nrhs, s, 0, 1, w_rho(c, s), inner);
+        return schur_pair(c, out, in, u, prec, false, nrhs, s, 0, 1, w_rho(c, s));
     }
     // Mhat^dagger = g5 Mhat(-sgn) g5
-    return schur_pair(c, out, in, u, prec, nd, nrhs, dagger ? -sgn : sgn, dagger, dagger, 0.0, inner);
+    return schur_pair(c, out, in, u, prec, nd, nrhs, dagger ? -sgn : sgn, dagger, dagger);
 }
 
 int op_mhat(tmx_ctx *c, SpinorPtr out, SpinorPtr in, int op, int prec, int dagger, int nrhs)
@@ -836,10 +830,9 @@ int tmx_destroy(tmx_ctx *c)
 {
     if (!c) return TMX_EINVAL;
     (void)hipStreamSynchronize(c->stream);
-    dev_free(c, c->clov[F16A]);
+    for (void *b : c->clov) dev_free(c, b);
     for (int p = 0; p < 3; ++p) {
         dev_free(c, c->links[p]);
-        dev_free(c, c->clov[p]);
         dev_free(c, c->inv[p]);
         dev_free(c, c->invnd[p]);
     }
@@ -908,7 +901,7 @@ int tmx_set_params(tmx_ctx *c, const tmx_params *p)
         !std::isfinite(p->mubar) || !std::isfinite(p->epsbar) || !std::isfinite(p->rho) || (p->t_bc != 1 && p->t_bc != -1))
         return set_err(c, TMX_EINVAL, "invalid parameters");
     if (c->have_params && !c->clover_from_host && (p->kappa != c->par.kappa || p->csw != c->par.csw))
-        c->clov_ok[0] = c->clov_ok[1] = c->clov_ok[2] = false;
+        for (bool &ok : c->clov_ok) ok = false;
     if (c->have_params && p->kappa != c->par.kappa) {
         // site inverses depend on 2 kappa mu
         c->inv_ok[0] = c->inv_ok[1] = c->inv_ok[2] = false;
@@ -942,9 +935,9 @@ int tmx_load_gauge(tmx_ctx *c, const double *host_links, double gauge_id)
     c->gauge_id = gauge_id;
     c->uploads++;
     // cascade: every derived field is stale now
+    for (bool &ok : c->clov_ok) ok = false;
     for (int p = 0; p < 3; ++p) {
         c->links_ok[p] = p == F64;
-        c->clov_ok[p] = false;
         c->inv_ok[p] = false;
         c->invnd_ok[p] = false;
     }
@@ -960,7 +953,7 @@ int tmx_load_clover(tmx_ctx *c, const double *host_T)
     if (!c->gauge_loaded) return set_err(c, TMX_ENOTLOADED, "load a gauge field first");
     if (!host_T) {
         c->clover_from_host = false;
-        c->clov_ok[0] = c->clov_ok[1] = c->clov_ok[2] = false;
+        for (bool &ok : c->clov_ok) ok = false;
         int r = ensure_clover(c, F64);
         if (r) return r;
         return hip_err(c, hipStreamSynchronize(c->stream), "clover build");
@@ -991,8 +984,8 @@ int tmx_load_clover(tmx_ctx *c, const double *host_T)
     dev_free(c, stage);
     if (e != hipSuccess) return hip_err(c, e, "clover upload");
     c->clover_from_host = true;
+    for (bool &ok : c->clov_ok) ok = false;
     c->clov_ok[F64] = true;
-    c->clov_ok[F32] = c->clov_ok[F16] = false;
     for (int p = 0; p < 3; ++p) c->inv_ok[p] = c->invnd_ok[p] = false;
     return TMX_OK;
 }
@@ -1073,22 +1066,18 @@ int tmx_apply_mhat_noalloc(tmx_ctx *c, void *out, const void *in, int op, int pr
                                           "-byte scratch (use tmx_apply_mhat)");
     // every derived field of this precision must exist already (building one
     // would allocate); rebuilding an existing one after new parameters does not
-    // (FP16 blocks only a solver has prepared are the structured ones of its
-    // iterations)
-    const bool inner = clover_slot(c, prec, false) == F16A && !c->clov[F16A];
-    const int slot = clover_slot(c, prec, inner);
-    const bool inv = nd ? (c->invnd[F64] && c->invnd[prec]) : (c->inv[F64] && c->inv[prec]);
-    const bool have = c->gauge_loaded && c->have_params && c->links[prec] && c->clov[F64] && c->clov[slot];
-    if (!have || !(nd ? inv : c->ready1[prec]) || (!inv && !can_solve(c, slot, nd)))
+    const bool have = c->gauge_loaded && c->have_params && c->links[prec] && c->clov[F64] &&
+                      c->clov[clover_slot(c, prec, false)] &&
+                      (nd ? (c->invnd[F64] && c->invnd[prec]) : (c->inv[F64] && c->inv[prec]));
+    if (!have)
         return set_err(c, TMX_ENOTLOADED, "tmx_apply_mhat_noalloc: the fields of this precision are not resident "
                                           "(one tmx_apply_mhat in this precision and sector builds them)");
-    // without a resident inverse the blocks are inverted in the kernel for any nrhs
-    r = ensure_ready(c, prec, nd, inv ? nrhs : 1, inner);
+    r = ensure_ready(c, prec, nd, nrhs);
     if (r) return r;
     void *u = scratch_address(c);
     if (!u) return TMX_EHIP;
     const SpinorPtr O = make_spinor(out, prec, nf, stride), I = make_spinor(const_cast<void *>(in), prec, nf, stride);
-    return mhat_with(c, O, I, make_spinor(u, prec, nf, stride), op, prec, dagger ? 1 : 0, nrhs, inner);
+    return mhat_with(c, O, I, make_spinor(u, prec, nf, stride), op, prec, dagger ? 1 : 0, nrhs);
 }
 
 int tmx_apply_mdagm(tmx_ctx *c, void *out, const void *in, int op, int prec, int nrhs)

@@ -57,7 +57,7 @@ struct LaunchCfg {
 
 constexpr size_t MAIL_BYTES = 4096;
 
-// block slot after the three precisions: FP16 blocks holding A itself
+// block slot after the three precisions: FP16 blocks in the general form
 constexpr int F16A = 3;
 
 // learned-preconditioner state (nn.hip)
@@ -85,8 +85,7 @@ struct tmx_ctx {
 
     // A = 1 + T on both parities, per block slot (a precision, or F16A):
     // structured blocks when built from the links, general Hermitian ones
-    // when given by the caller; F16A is the general FP16 copy of a clover
-    // term built from the links
+    // when given by the caller; F16 is always structured, F16A always general
     void *clov[4] = {nullptr, nullptr, nullptr, nullptr};
     bool clov_ok[4] = {false, false, false, false};
     bool clover_from_host = false;
@@ -95,7 +94,6 @@ struct tmx_ctx {
     // degenerate site inverse (A_ee + i nu g5)^{-1}, per precision
     void *inv[3] = {nullptr, nullptr, nullptr};
     bool inv_ok[3] = {false, false, false};
-    bool ready1[3] = {false, false, false};  // the one-flavour operator of a precision has been prepared once
     double inv_nu = 0;
 
     // two-flavour inverse factor (A_ee^2 + nubar^2 - epst^2)^{-1}
