@@ -41,7 +41,7 @@ int hip_err(tmx_ctx *c, hipError_t e, const char *where)
                    std::string(where) + ": " + hipGetErrorString(e));
 }
 
-void *dev_alloc(tmx_ctx *c, size_t bytes)
+static void *alloc_once(tmx_ctx *c, size_t bytes)
 {
     void *p = nullptr;
     if (bytes == 0) bytes = 16;
@@ -89,11 +89,35 @@ static void ws_drop(tmx_ctx *c, Workspace &w)
     w.bytes = 0;
 }
 
-static void *ws_take(tmx_ctx *c, const std::string &name, size_t bytes)
+bool drop_spares(tmx_ctx *c)
+{
+    if (c->spare_busy) return false;
+    bool any = false;
+    for (auto &kv : c->ws) any = any || (kv.second.spare && kv.second.p);
+    if (!any) return false;
+    (void)hipStreamSynchronize(c->stream);
+    for (auto &kv : c->ws)
+        if (kv.second.spare && kv.second.p) ws_drop(c, kv.second);
+    return true;
+}
+
+void *dev_alloc(tmx_ctx *c, size_t bytes)
+{
+    const std::string err = c->err;
+    void *p = alloc_once(c, bytes);
+    if (!p && drop_spares(c)) {
+        p = alloc_once(c, bytes);
+        if (p) c->err = err;
+    }
+    return p;
+}
+
+static void *ws_take(tmx_ctx *c, const std::string &name, size_t bytes, bool spare)
 {
     Workspace &w = c->ws[name];
     if (w.bytes >= bytes && w.p) return w.p;
-    if (c->ws_limit && c->ws_bytes - w.bytes + bytes > c->ws_limit) {
+    auto over = [&] { return c->ws_limit && c->ws_bytes - w.bytes + bytes > c->ws_limit; };
+    if (over() && (spare || !drop_spares(c) || over())) {
         set_err(c, TMX_ENOMEM, "workspace '" + name + "' of " + std::to_string(bytes) +
                                    " bytes exceeds the workspace limit (TMX_WS_LIMIT)");
         return nullptr;
@@ -102,7 +126,7 @@ static void *ws_take(tmx_ctx *c, const std::string &name, size_t bytes)
         (void)hipStreamSynchronize(c->stream);
         ws_drop(c, w);
     }
-    w.p = dev_alloc(c, bytes);
+    w.p = spare ? alloc_once(c, bytes) : dev_alloc(c, bytes);
     if (w.p) {
         w.bytes = bytes;
         c->ws_bytes += bytes;
@@ -110,24 +134,17 @@ static void *ws_take(tmx_ctx *c, const std::string &name, size_t bytes)
     return w.p;
 }
 
-void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes)
-{
-    void *p = ws_take(c, name, bytes);
-    if (p || c->spare_busy) return p;
-    bool any = false;
-    for (auto &kv : c->ws) any = any || (kv.second.spare && kv.second.p);
-    if (!any) return nullptr;
-    (void)hipStreamSynchronize(c->stream);
-    for (auto &kv : c->ws)
-        if (kv.second.spare && kv.second.p) ws_drop(c, kv.second);
-    return ws_take(c, name, bytes);
-}
+void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes) { return ws_take(c, name, bytes, false); }
 
 void *ws_spare(tmx_ctx *c, const std::string &name, size_t bytes)
 {
+    size_t held = 0;
+    for (auto &kv : c->ws)
+        if (kv.second.spare && kv.first != name) held += kv.second.bytes;
+    if (held + bytes > c->spare_limit) return nullptr;
     const std::string err = c->err;
     c->ws[name].spare = true;
-    void *p = ws_take(c, name, bytes);
+    void *p = ws_take(c, name, bytes, true);
     if (!p) c->err = err;
     return p;
 }
@@ -809,6 +826,9 @@ int tmx_create(const int dims[4], void *hip_stream, tmx_ctx **out)
     // device (resolved here, at set-up; a failure only disables that entry point)
     (void)scratch_address(c);
     c->err.clear();
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) (void)hipGetLastError();
+    c->spare_limit = total / 8;
     // cap on the named scratch buffers (bytes), for callers that budget HBM
     if (const char *e = std::getenv("TMX_WS_LIMIT")) c->ws_limit = std::strtoull(e, nullptr, 10);
     const char *tr = std::getenv("TMX_TRACE");

@@ -1299,29 +1299,24 @@ static int reserve_cg(Sys &S, int prec)
     return reserve_operator(S, prec);
 }
 
-// FP64 residual, x_k and p_k of the stage as spare buffers; false if they and
-// the batch's residuals would take more than an eighth of the device (the
-// context keeps them between calls) or there is no room
+// FP64 residual, x_k and p_k of the stage as spare buffers; false if there is
+// no room for them, or for them and the batch's residuals within the context's
+// share of spare memory
 static bool spare_shift_fields(Sys &S, int ns, std::vector<SpinorPtr> &xs, std::vector<SpinorPtr> &ps, SpinorPtr &r)
 {
     tmx_ctx *c = S.c;
     const size_t fb = spinor_field_bytes(F64, S.nf, c->Vh);
-    size_t avail = 0, total = 0;
-    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if ((2 * ns + MS_BATCH) * fb > total / 8) return false;
-    const SpareUse spare(c);
+    if ((2 * ns + MS_BATCH) * fb > c->spare_limit) return false;
     auto get = [&](const std::string &name, SpinorPtr &f) {
         void *d = ws_spare(c, name, fb);
         f = make_spinor(d, F64, S.nf, c->Vh);
         return d != nullptr;
     };
-    if (!get("sv_ms64_r", r)) return false;
+    bool ok = get("sv_ms64_r", r);
     for (int k = 0; k < ns; ++k)
-        if (!get("sv_ms64_x" + std::to_string(k), xs[k]) || !get("sv_ms64_p" + std::to_string(k), ps[k])) return false;
-    return true;
+        ok = ok && get("sv_ms64_x" + std::to_string(k), xs[k]) && get("sv_ms64_p" + std::to_string(k), ps[k]);
+    if (!ok) (void)drop_spares(c);  // part of them is of no use
+    return ok;
 }
 
 // The batched multishift solve of B (packed FP64) for every shift: one

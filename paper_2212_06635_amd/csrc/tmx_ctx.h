@@ -112,6 +112,7 @@ struct tmx_ctx {
     std::map<std::string, tmx::Workspace> ws;
     size_t ws_bytes = 0;  // bytes held by the named scratch buffers
     size_t ws_limit = 0;  // cap on ws_bytes (0: none), from TMX_WS_LIMIT
+    size_t spare_limit = 0;   // cap on the spare ones among them
     bool spare_busy = false;  // the spare buffers are in use
 
     // device allocator: the caller's hook (tmx_set_allocator) or hipMalloc
@@ -161,10 +162,12 @@ void *dev_alloc(tmx_ctx *c, size_t bytes);
 void dev_free(tmx_ctx *c, void *p);
 void *ws_get(tmx_ctx *c, const std::string &name, size_t bytes);
 // A buffer that only makes a call faster: nullptr, without an error, if there
-// is no room.  Spare buffers are given back whenever ws_get would otherwise
-// fail, unless their user has set spare_busy (it then takes every buffer it
-// cannot do without before the spare ones).
+// is no room, or the context would keep more than an eighth of the device in
+// such buffers.  Spare buffers are given back whenever dev_alloc or ws_get
+// would otherwise fail, unless their user has set spare_busy (it then takes
+// every buffer it cannot do without before the spare ones).
 void *ws_spare(tmx_ctx *c, const std::string &name, size_t bytes);
+bool drop_spares(tmx_ctx *c);  // false: none held, or in use
 
 // Site blocks in FP16.  The operator entry points round A = 1 + T and its
 // inverse to binary16, as their callers' fields expect; an iteration inside a
