@@ -361,6 +361,14 @@ static __global__ void __launch_bounds__(256) cg_step_end_kernel(const double *p
     if (stop) s->stop = it;
 }
 
+// Every way out of a solve waits for what it has enqueued ahead (an error of a
+// reliable update, say): those launches read the state, which the next call
+// may set from another stream.
+struct CgDrain {
+    hipStream_t st;
+    ~CgDrain() { (void)hipStreamSynchronize(st); }
+};
+
 // wait for the result of iteration it
 static int cg_wait(tmx_ctx *c, int it, const CgMail *dev_ring, CgMail *out)
 {
@@ -564,6 +572,7 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
     const int ahead = c->mail_dev && !c->kstats_on ? 1 : 0;
     int it = 0, issued = 0;  // iterations whose result has been read, and enqueued
     bool tr_current = true;  // tr holds the true residual of x
+    const CgDrain drain{c->stream};
     if (nactive > 0) TRY(set_state());
     while (nactive > 0 && it < maxiter) {
         while (issued < maxiter && issued <= it + ahead) TRY(enqueue(issued++));
