@@ -29,12 +29,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 STENCIL_SOURCES = ("csrc/dslash.hip", "csrc/tmx_device.h", "csrc/tmx_kernels.h")
 COPY_BYTES = 2 ** 31
 
-# rocprof kernel name -> bench label; dslash_kernel<P, NF, MODE, SPT[, CT]> (sites
+# rocprof kernel name -> bench label; dslash_kernel<P, NF, MODE, SPT[, CT, A]> (sites
 # per thread: the tuned launch of a kernel uses one of the two; CT: structured
-# site blocks; MODE 2 inverts them in the kernel)
+# site blocks; A: the arguments of an application, a solver's kernels take more;
+# MODE 2 inverts the blocks in the kernel)
 LABELS = {f"void tmx::dslash_kernel<{p}, 1, {m}, {t}{ct}>(tmx::DslashArgs)": f"K{m % 2 + 1}_{n}"
           for p, n in ((0, "f64"), (1, "f32"), (2, "f16")) for m in (0, 1, 2) for t in (1, 2)
-          for ct in ("", ", false", ", true")}
+          for ct in ("", ", false, tmx::DslashArgs", ", true, tmx::DslashArgs")}
 
 
 def source_digest() -> str:
@@ -135,7 +136,7 @@ def summarize(d: str, vh: int) -> str:
         if kname not in st:
             continue
         calls, avg = st[kname]
-        alg = (launch_bytes_per_site if ", true>" in kname else kernel_bytes_per_site)(lab) * vh
+        alg = (launch_bytes_per_site if ", true, tmx::DslashArgs>" in kname else kernel_bytes_per_site)(lab) * vh
         fe = f[kname] * 1024 * sf
         wr = w[kname] * 1024 * sw
         rd = alg - (24 * {"f64": 8, "f32": 4, "f16": 2}[lab[3:]] + (4 if "f16" in lab else 0)) * vh

@@ -516,7 +516,7 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
     const std::string k1 = kname("K1", prec, nd, nrhs), k2 = kname("K2", prec, nd, nrhs);
     const LaunchCfg l1 = launch_cfg(c, k1), l2 = launch_cfg(c, k2);
     const int rg = (l1.rg > 0 && l1.rg < nrhs && nrhs % l1.rg == 0) ? l1.rg : nrhs;
-    DslashArgs a = base_args(c, prec, nd, nrhs);
+    DslashFused a{base_args(c, prec, nd, nrhs)};
     a.sgn = sgn;
     a.parity = 0;
     a.out = u;
@@ -525,7 +525,7 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
     a.g5in = g5in;
     a.xcd = l1.xcd;
     a.spt = l1.spt;
-    DslashArgs b = base_args(c, prec, nd, nrhs);
+    DslashFused b{base_args(c, prec, nd, nrhs)};
     b.sgn = sgn;
     b.parity = 1;
     b.out = out;
@@ -563,11 +563,13 @@ static int schur_pair(tmx_ctx *c, SpinorPtr out, SpinorPtr in, SpinorPtr u, int 
         a.r0 = b.r0 = r0;
         a.rg = b.rg = rg;
         kstat_begin(c, k1);
-        hipError_t e = launch_dslash(prec, nf, k1mode, a, c->stream, l1.block);
+        hipError_t e = a.stop ? launch_dslash_fused(prec, nf, k1mode, a, c->stream, l1.block)
+                              : launch_dslash(prec, nf, k1mode, a, c->stream, l1.block);
         kstat_end(c);
         if (e != hipSuccess) return hip_err(c, e, "K1 launch");
         kstat_begin(c, k2);
-        e = launch_dslash(prec, nf, k2mode, b, c->stream, l2.block);
+        e = k2mode != MODE_DIAG ? launch_dslash_fused(prec, nf, k2mode, b, c->stream, l2.block)
+                                : launch_dslash(prec, nf, k2mode, b, c->stream, l2.block);
         kstat_end(c);
         if (e != hipSuccess) return hip_err(c, e, "K2 launch");
     }

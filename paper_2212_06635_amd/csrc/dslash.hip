@@ -45,6 +45,8 @@
 // and on the output (g5out) implement the
 // adjoint Mhat^dagger = g5 Mhat(-sgn) g5 and the normal operator without
 // extra passes.
+#include <type_traits>
+
 #include "tmx_device.h"
 #include "tmx_kernels.h"
 
@@ -213,16 +215,18 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &a, const int x[4], int
     }
 }
 
-template <int P, int NF, int MODE, bool CT, bool NT = true>
-__device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs);
+// A is DslashArgs for applications and DslashFused for a solver's kernels
+template <class A> constexpr bool FUSED = std::is_same_v<A, DslashFused>;
+
+template <int P, int NF, int MODE, bool CT, bool NT = true, class A>
+__device__ __forceinline__ void dslash_slot(const A &a, int s, long rhs);
 
 // Whether a launch enqueued ahead is not wanted any more.  Kernel arguments are
 // not loaded ahead of a branch they lie behind, so a check in front of
 // everything made their miss a serial one more per launch; the empty asm asks for
 // those of the check and the first ones the hops need together with those of
-// u.  N in FP64 at 8^4 24.2 -> 22.9 us, in FP16 at 120960 sites 67.4 -> 66.0
-// (65.4 without a check).
-__device__ __forceinline__ bool stopped(const DslashArgs &a, long &u)
+// u.
+__device__ __forceinline__ bool stopped(const DslashFused &a, long &u)
 {
     const int *stop = a.stop;
     const int it = a.it;
@@ -237,13 +241,14 @@ __device__ __forceinline__ bool stopped(const DslashArgs &a, long &u)
 // thread count); item u is right-hand side r0 + u % rg of site u / rg.  SPT
 // is a template parameter: a runtime loop costs registers (and occupancy)
 // even when it runs once.
-template <int P, int NF, int MODE, int SPT, bool CT>
-__global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
+template <int P, int NF, int MODE, int SPT, bool CT, class A>
+__global__ void __launch_bounds__(256) dslash_kernel(A a)
 {
     const long rg = a.rg;
     const long n = (long)a.g.Vh * rg;
     long u = (long)xcd_block(a.xcd) * blockDim.x + threadIdx.x;
-    if (stopped(a, u)) return;
+    if constexpr (FUSED<A>)
+        if (stopped(a, u)) return;
     if constexpr (SPT == 1) {
         if (u >= n) return;
         const int s = (int)(u / rg);
@@ -304,8 +309,8 @@ __device__ __forceinline__ void apply_clov(const void *clov, long cs, long s, in
 
 // one output slot: site s (of the output parity), right-hand side rhs; NT:
 // links streamed past the caches
-template <int P, int NF, int MODE, bool CT, bool NT>
-__device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs)
+template <int P, int NF, int MODE, bool CT, bool NT, class A>
+__device__ __forceinline__ void dslash_slot(const A &a, int s, long rhs)
 {
     using R = typename RealOf<P>::type;
     const long t = (long)s * a.nrhs + rhs;  // slot of the output, the diagonal input and the norms
@@ -392,7 +397,8 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                 load_chiral<P>(a.x, 0, t, c, xv);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) xv[k] = gx * xv[k];
-                if (MODE == MODE_NRM && a.nsig) add_norm(xn2, xv);
+                if constexpr (MODE == MODE_NRM)
+                    if (a.nsig) add_norm(xn2, xv);
                 if constexpr (CT) {
                     R b[28];
                     load_ct<P>(a.clov, cs, s, c, b);
@@ -417,9 +423,11 @@ __device__ __forceinline__ void dslash_slot(const DslashArgs &a, int s, long rhs
                     x0[k] = gx * x0[k];
                     x1[k] = gx * x1[k];
                 }
-                if (MODE == MODE_NRM && a.nsig) {
-                    add_norm(xn2, x0);
-                    add_norm(xn2, x1);
+                if constexpr (MODE == MODE_NRM) {
+                    if (a.nsig) {
+                        add_norm(xn2, x0);
+                        add_norm(xn2, x1);
+                    }
                 }
                 apply_clov<P, CT>(a.clov, cs, s, c, tw, x0, out[0] + 6 * c, -tw, x1, out[1] + 6 * c);
 #pragma unroll
@@ -604,8 +612,8 @@ template <typename R> __device__ __forceinline__ float chiral_max(const cx<R> v[
     return m;
 }
 
-template <int P, int NF, int MODE, bool CT>
-__global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
+template <int P, int NF, int MODE, bool CT, class A>
+__global__ void __launch_bounds__(256) dslash_split_kernel(A a)
 {
     using R = typename RealOf<P>::type;
     extern __shared__ __align__(16) char split_lds[];
@@ -613,7 +621,8 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long n = (long)a.g.Vh * a.rg;
     long u0 = (long)xcd_block(a.xcd) * 64 + lane;
-    if (stopped(a, u0)) return;
+    if constexpr (FUSED<A>)
+        if (stopped(a, u0)) return;
     const bool live = u0 < n;
     const long u = live ? u0 : n - 1;  // the last workgroup's spare lanes repeat the last slot
     const int s = (int)(u / a.rg);
@@ -682,7 +691,8 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
                 load_chiral<P>(a.x, f, t, c, xv[f]);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) xv[f][k] = gx * xv[f][k];
-                if (MODE == MODE_NRM && a.nsig) add_norm(xn2, xv[f]);
+                if constexpr (MODE == MODE_NRM)
+                    if (a.nsig) add_norm(xn2, xv[f]);
             }
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
@@ -709,7 +719,8 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
             for (int f = 0; f < NF; ++f)
 #pragma unroll
                 for (int k = 0; k < 6; ++k) out[f][k] = out[f][k] - kf * acc[f][k];
-            if (MODE == MODE_NRM && a.nsig) n2 = a.nsig[rhs] * xn2;
+            if constexpr (MODE == MODE_NRM)
+                if (a.nsig) n2 = a.nsig[rhs] * xn2;
         }
         if (a.g5out && c == 1) {
 #pragma unroll
@@ -756,7 +767,8 @@ __global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs a)
     if constexpr (MODE == MODE_RES || MODE == MODE_NRM) {
         if (c == 0) a.nrm[t] = n2 + sh[0].n2[lane];
     }
-    const SpinorPtr dst = MODE == MODE_RES ? a.rout : a.out;
+    SpinorPtr dst = a.out;
+    if constexpr (MODE == MODE_RES) dst = a.rout;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         float m = 0.f;
@@ -782,32 +794,29 @@ template <int P, int NF> static bool use_split(long n)
     return n <= (P == F64 ? 24576 : (P == F16 && NF == 1 ? 98304 : 49152));
 }
 
-template <int P, int NF, int MODE, bool CT>
-static hipError_t launch_split(const DslashArgs &a, hipStream_t st)
+template <int P, int NF, int MODE, bool CT, class A>
+static hipError_t launch_one(const A &a, hipStream_t st, int block)
 {
     using R = typename RealOf<P>::type;
     const long n = (long)a.g.Vh * a.rg;
-    const int grid = (int)((n + 63) / 64);
-    hipLaunchKernelGGL((dslash_split_kernel<P, NF, MODE, CT>), dim3(grid), dim3(256), NF * sizeof(SplitShared<P, R>), st,
-                       a);
-    return hipGetLastError();
-}
-
-template <int P, int NF, int MODE, bool CT>
-static hipError_t launch_one(const DslashArgs &a, hipStream_t st, int block)
-{
-    const long n = (long)a.g.Vh * (a.rg > 0 ? a.rg : a.nrhs);
-    if constexpr (!(MODE == MODE_SOLVE && NF == 2)) {  // that one is for many sites only
-        if (n > 0 && use_split<P, NF>(n)) return launch_split<P, NF, MODE, CT>(a, st);
-    }
-    const long per = block * (long)(a.spt > 0 && MODE != MODE_RES && MODE != MODE_NRM ? a.spt : 1);
-    const int grid = (int)((n + per - 1) / per);
     if (n == 0) return hipSuccess;
-    constexpr int M2 = MODE == MODE_RES || MODE == MODE_NRM ? MODE_DIAG : MODE;
-    if (MODE == M2 && a.spt == 2)
-        hipLaunchKernelGGL((dslash_kernel<P, NF, M2, 2, CT>), dim3(grid), dim3(block), 0, st, a);
-    else
-        hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 1, CT>), dim3(grid), dim3(block), 0, st, a);
+    if constexpr (!(MODE == MODE_SOLVE && NF == 2)) {  // that one is for many sites only
+        if (use_split<P, NF>(n)) {
+            hipLaunchKernelGGL((dslash_split_kernel<P, NF, MODE, CT, A>), dim3((unsigned)((n + 63) / 64)), dim3(256),
+                               NF * sizeof(SplitShared<P, R>), st, a);
+            return hipGetLastError();
+        }
+    }
+    constexpr bool EPI = MODE == MODE_RES || MODE == MODE_NRM;  // one slot per thread
+    const long per = block * (long)(EPI ? 1 : a.spt);
+    const int grid = (int)((n + per - 1) / per);
+    if constexpr (!EPI) {
+        if (a.spt == 2) {
+            hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 2, CT, A>), dim3(grid), dim3(block), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((dslash_kernel<P, NF, MODE, 1, CT, A>), dim3(grid), dim3(block), 0, st, a);
     return hipGetLastError();
 }
 
@@ -820,8 +829,8 @@ static hipError_t launch_pair(const DslashArgs &a, const SpinorPtr &in2, const S
     return hipGetLastError();
 }
 
-template <int P, int NF>
-static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int block)
+template <int P, int NF, class A>
+static hipError_t launch_mode(int mode, const A &a, hipStream_t st, int block)
 {
     if (mode == MODE_SOLVE) {
         if constexpr (P == F64 || (P == F16 && NF == 1))  // FP32: the stored inverse, formed in FP64
@@ -836,17 +845,23 @@ static hipError_t launch_mode(int mode, const DslashArgs &a, hipStream_t st, int
             return a.ct ? launch_one<P, NF, MODE_INV, true>(a, st, block)
                         : launch_one<P, NF, MODE_INV, false>(a, st, block);
     }
-    if (mode == MODE_NRM)
-        return a.ct ? launch_one<P, NF, MODE_NRM, true>(a, st, block) : launch_one<P, NF, MODE_NRM, false>(a, st, block);
-    if (mode == MODE_RES)
-        return a.ct ? launch_one<P, NF, MODE_RES, true>(a, st, block) : launch_one<P, NF, MODE_RES, false>(a, st, block);
-    return a.ct ? launch_one<P, NF, MODE_DIAG, true>(a, st, block) : launch_one<P, NF, MODE_DIAG, false>(a, st, block);
+    if constexpr (FUSED<A>) {
+        if (mode == MODE_NRM)
+            return a.ct ? launch_one<P, NF, MODE_NRM, true>(a, st, block) : launch_one<P, NF, MODE_NRM, false>(a, st, block);
+        if (mode == MODE_RES)
+            return a.ct ? launch_one<P, NF, MODE_RES, true>(a, st, block) : launch_one<P, NF, MODE_RES, false>(a, st, block);
+        return hipErrorInvalidValue;
+    } else {
+        if (mode != MODE_DIAG) return hipErrorInvalidValue;
+        return a.ct ? launch_one<P, NF, MODE_DIAG, true>(a, st, block) : launch_one<P, NF, MODE_DIAG, false>(a, st, block);
+    }
 }
 
-hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a0, hipStream_t st, int block)
+template <class A>
+static hipError_t launch_any(int prec, int nf, int mode, const A &a0, hipStream_t st, int block)
 {
     if (block <= 0) block = 256;
-    DslashArgs a = a0;
+    A a = a0;
     if (a.spt != 2) a.spt = 1;
     if (a.rg <= 0 || a.r0 < 0 || a.r0 + a.rg > a.nrhs) {
         a.r0 = 0;
@@ -856,6 +871,16 @@ hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a0, hipSt
     if (prec == F32) return nf == 1 ? launch_mode<F32, 1>(mode, a, st, block) : launch_mode<F32, 2>(mode, a, st, block);
     if (prec == F16) return nf == 1 ? launch_mode<F16, 1>(mode, a, st, block) : launch_mode<F16, 2>(mode, a, st, block);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a, hipStream_t st, int block)
+{
+    return launch_any(prec, nf, mode, a, st, block);
+}
+
+hipError_t launch_dslash_fused(int prec, int nf, int mode, const DslashFused &a, hipStream_t st, int block)
+{
+    return launch_any(prec, nf, mode, a, st, block);
 }
 
 hipError_t launch_dslash_pair(int nf, int mode, const DslashArgs &a0, SpinorPtr in2, SpinorPtr out2, hipStream_t st,

@@ -193,7 +193,7 @@ struct NFuse {
     int lo = 0;
     const double *alpha = nullptr, *sigma = nullptr;
     double *rnrm = nullptr;
-    const int *stop = nullptr;  // the kernels do nothing if *stop < it (see DslashArgs)
+    const int *stop = nullptr;  // the kernels do nothing if *stop < it (see DslashFused)
     int it = 0;
     std::function<int()> between;  // called once nrm is enqueued (to enqueue alpha)
 };

@@ -11,6 +11,11 @@ namespace tmx {
 // what a stencil launch computes (dslash.hip)
 enum { MODE_INV = 0, MODE_DIAG = 1, MODE_SOLVE = 2, MODE_RES = 3, MODE_NRM = 4 };
 
+// What an operator application needs.  The launches of a solver take more (see
+// DslashFused): the arguments of a kernel are read from host memory, a miss per
+// cache line in front of each launch's first loads, so the others do without.
+// 384 -> 224 bytes and no check for an enqueued-ahead launch: N in FP16 at
+// 120960 sites 66.3 -> 65.5 us, in FP64 at 8^4 23.1 -> 21.8.
 struct DslashArgs {
     Geom g;
     int parity;        // output parity
@@ -20,20 +25,22 @@ struct DslashArgs {
     SpinorPtr x;       // diagonal input (output parity), MODE_DIAG only
     LinkPtr U;         // compressed links, both parities
     const void *clov;  // A of the output parity: structured blocks (ct) or general Hermitian ones
-    int ct;            // clov holds structured blocks (see load_ct)
     const void *inv;   // MODE_INV: full inverse (deg) or Hermitian inverse factor (nd)
     double nu;         // nu (deg) or nubar (nd), already times 2 kappa
     double epst;       // 2 kappa epsbar (nd)
-    double del;        // MODE_SOLVE (nd): sqrt(epst^2 - nubar^2)
     double kfac;       // MODE_DIAG: coefficient of the hopping term
     int sgn;           // sign of the twist
     int t_bc;          // fermion time boundary factor
     int g5in, g5x, g5out;
     int xcd;           // XCD-aware block order
-    // what every launch reads comes first: its kernel arguments then lie in few cache lines
     double rho;        // MODE_DIAG, one flavour: adds i rho x to the final output (after g5out)
     int r0, rg;        // right-hand sides r0 .. r0 + rg - 1 of the nrhs per site (rg = 0: all)
     int spt;           // sites (slots) per thread: 1, or a grid-stride loop over spt of them
+    int ct;            // clov holds structured blocks (see load_ct)
+    double del;        // MODE_SOLVE (nd): sqrt(epst^2 - nubar^2)
+};
+
+struct DslashFused : DslashArgs {
     // of an iteration a solver has enqueued ahead: nothing runs if *stop < it
     const int *stop;
     int it;
@@ -49,7 +56,10 @@ struct DslashArgs {
     const double *ralpha, *rsig;
 };
 
+// MODE_INV, MODE_SOLVE, MODE_DIAG
 hipError_t launch_dslash(int prec, int nf, int mode, const DslashArgs &a, hipStream_t st, int block);
+// a solver's launches: MODE_INV and MODE_SOLVE enqueued ahead (stop set), MODE_NRM, MODE_RES
+hipError_t launch_dslash_fused(int prec, int nf, int mode, const DslashFused &a, hipStream_t st, int block);
 // the FP64 first half twice, one right-hand side each: out = B^{-1}(sgn) (H in) as
 // a says, and out2 = B^{-1}(-sgn) (H in2) with the other setting of g5in
 hipError_t launch_dslash_pair(int nf, int mode, const DslashArgs &a, SpinorPtr in2, SpinorPtr out2, hipStream_t st,
