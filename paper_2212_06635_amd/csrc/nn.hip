@@ -2043,10 +2043,12 @@ static int pc_loss_grad(tmx_ctx *c, const double *b, const double *x, const int 
 {
     // (tiles of 64 sites, two per workgroup at a time)
     if (c->Vh >= 64 * WG_BLOCKS_MIN && !c->spare_busy) {
+        const std::string err = c->err;
         c->spare_busy = true;
         const int r = pc_loss_grad_blocks(c, b, x, idx, n, loss_kind, op, loss, WG_BLOCKS);
         c->spare_busy = false;
         if (r != TMX_ENOMEM) return r;
+        c->err = err;  // not the call's error (yet)
     }
     return pc_loss_grad_blocks(c, b, x, idx, n, loss_kind, op, loss, WG_BLOCKS_MIN);
 }
