@@ -295,13 +295,18 @@ static int ensure_clover(tmx_ctx *c, int slot)
 // Two flavours: A^2 + nubar^2 - epsbar^2 splits into two Hermitian factors
 // A +- del where nubar <= epsbar.  The two eliminations then replace the
 // stored inverse's 72 of K1's 196 reals a site (structured blocks), but the
-// FP64 kernel runs one wave per SIMD and cannot hide them: N in us, stored ->
-// solved
-//    65536 sites  173 -> 184
-//   331776 sites  717 -> 675
-//  1048576 sites 2129 -> 2037
-// hence the line; FP16 (a solver's inner operator, 216 VGPRs instead of 123)
-// is slower at every size: a solve at 331776 sites 32.5 -> 34.7 ms.
+// FP64 kernel runs one wave per SIMD and cannot hide them: N in us and a CG in
+// ms, stored -> solved
+//    43008 sites  107 -> 105   14.8 -> 14.7
+//    65536 sites  149 -> 171   20.4 -> 22.6
+//    81920 sites  217 -> 210   28.9 -> 28.2
+//    98304 sites  235 -> 221   32.0 -> 30.2
+//   122880 sites  256 -> 242   34.5 -> 33.0
+//   331776 sites  716 -> 677   94.8 -> 90.5
+// (65536 sites are one wave on each of the 1024 SIMDs: one round, in which the
+// longer kernel shows in full) hence the line; FP16 (a solver's inner operator,
+// 216 VGPRs instead of 123) is slower at every size: a solve at 331776 sites
+// 32.5 -> 34.7 ms.
 // FP32 reads the stored inverse, formed in FP64 and rounded once.  An
 // elimination on blocks rounded to FP32 carries that rounding times the
 // block's condition number, the stored inverse does not: against 64 bits one
@@ -310,7 +315,7 @@ static int ensure_clover(tmx_ctx *c, int slot)
 // fields but 100 times on rough ones.  In FP64 the eliminations' error is the
 // smaller one on every field: the stored inverse goes through A^2 (2.2e-16
 // against 3.2e-16 smooth, 1e-14 against 1e-11 rough).
-constexpr int ND_SOLVE_SITES = 98304;
+constexpr int ND_SOLVE_SITES = 73728;
 static double nd_square(const tmx_ctx *c)
 {
     const double nb = 2.0 * c->par.kappa * c->par.mubar, ep = 2.0 * c->par.kappa * c->par.epsbar;

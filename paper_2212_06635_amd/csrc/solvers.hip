@@ -1281,12 +1281,21 @@ static int check_shifts(tmx_ctx *c, const double *shifts, int nshift)
 // eight take as many iterations as the stage itself.  With the shifted systems
 // updated in batches an FP64 stage costs about two low-precision iterations
 // per iteration and takes every shift to its tolerance at once; the refinement
-// only checks.  12 shifts of the two-flavour operator at 24^3x48, FP32 / FP16
-// inner precision: 291 / 306 ms with the low-precision stage, 135 ms with this
-// one; 4 shifts 112 / 103 against 117 ms, 6 shifts 158 / 156 against 121 ms.
-// On small lattices, where launches and latency cost the same in every
-// precision, it wins from 3 shifts on (8^4, one flavour, 4 shifts: 7.5 / 10.1
-// against 3.9 ms).
+// only checks.  Shifts over four decades, ms with the FP32 / FP16 stage ->
+// with this one, one flavour, then two:
+//                       3 shifts            4 shifts            5 shifts            8 shifts
+//    2048 sites    4.5/5.8 -> 3.3      5.6/7.6 -> 3.4      6.5/9.4 -> 3.5      9.6/15  -> 3.8
+//                  6.5/8.3 -> 4.9      7.9/11  -> 5.1      9.4/14  -> 5.2      14/21   -> 5.6
+//   16384 sites    7.3/8.2 -> 5.6      8.8/11  -> 5.8      10/13   -> 6.0      15/21   -> 6.4
+//                   11/13  -> 9.6       13/16  -> 9.8      16/20   -> 10       23/32   -> 11
+//   27648 sites    8.4/9.4 -> 7.8       10/12  -> 8.0      12/15   -> 8.2      18/24   -> 8.8
+//                   14/15  -> 15        17/20  -> 15       20/25   -> 15       29/39   -> 16
+//   65536 sites     13/13  -> 12        16/17  -> 12       19/21   -> 12       28/33   -> 13
+//                   23/26  -> 28        28/33  -> 29       33/41   -> 29       48/65   -> 31
+//  331776 sites     44/38  -> 47        55/51  -> 48       65/63   -> 49       97/100  -> 52
+//                   84/76  -> 113      103/99  -> 116     122/123  -> 118     181/195  -> 125
+// From five shifts it is the faster one everywhere; up to 16384 sites, where
+// launches and latency cost the same in every precision, from three.
 static bool ms_f64_stage(const tmx_ctx *c, int nshift) { return nshift >= (c->Vh <= 16384 ? 3 : 5); }
 // the stage stops at this fraction of the tolerance: the true residual differs
 // from the iterated one by rounding, and the refinement it replaces ended its
