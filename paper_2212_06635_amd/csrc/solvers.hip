@@ -366,7 +366,11 @@ static __global__ void __launch_bounds__(256) cg_step_end_kernel(const double *p
 // may set from another stream.
 struct CgDrain {
     hipStream_t st;
-    ~CgDrain() { (void)hipStreamSynchronize(st); }
+    bool done = false;
+    ~CgDrain()
+    {
+        if (!done) (void)hipStreamSynchronize(st);
+    }
 };
 
 // wait for the result of iteration it
@@ -572,7 +576,7 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
     const int ahead = c->mail_dev && !c->kstats_on ? 1 : 0;
     int it = 0, issued = 0;  // iterations whose result has been read, and enqueued
     bool tr_current = true;  // tr holds the true residual of x
-    const CgDrain drain{c->stream};
+    CgDrain drain{c->stream};
     if (nactive > 0) TRY(set_state());
     while (nactive > 0 && it < maxiter) {
         while (issued < maxiter && issued <= it + ahead) TRY(enqueue(issued++));
@@ -635,6 +639,7 @@ static int cg_core(Sys &S, SpinorPtr x, SpinorPtr b, int cols, const double *sig
     }
     // FP64 true residual (a last reliable update has just taken it)
     if (!tr_current) TRY(true_residual<P>(S, r, rl, false, b, x, sigma, cols, tr));
+    drain.done = true;  // either residual's readback waited for the stream
     const double t1 = now_seconds();
     int rc = TMX_OK;
     for (int k = 0; k < cols; ++k) {

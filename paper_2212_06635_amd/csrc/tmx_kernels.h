@@ -14,8 +14,8 @@ enum { MODE_INV = 0, MODE_DIAG = 1, MODE_SOLVE = 2, MODE_RES = 3, MODE_NRM = 4 }
 // What an operator application needs.  The launches of a solver take more (see
 // DslashFused): the arguments of a kernel are read from host memory, a miss per
 // cache line in front of each launch's first loads, so the others do without.
-// 384 -> 224 bytes and no check for an enqueued-ahead launch: N in FP16 at
-// 120960 sites 66.3 -> 65.5 us, in FP64 at 8^4 23.1 -> 21.8.
+// 384 -> 232 bytes and no check for an enqueued-ahead launch: N in FP16 at
+// 120960 sites 66.3 -> 65.5 us, in FP64 at 8^4 22.2 -> 21.6.
 struct DslashArgs {
     Geom g;
     int parity;        // output parity
@@ -25,9 +25,11 @@ struct DslashArgs {
     SpinorPtr x;       // diagonal input (output parity), MODE_DIAG only
     LinkPtr U;         // compressed links, both parities
     const void *clov;  // A of the output parity: structured blocks (ct) or general Hermitian ones
+    int ct;            // clov holds structured blocks (see load_ct)
     const void *inv;   // MODE_INV: full inverse (deg) or Hermitian inverse factor (nd)
     double nu;         // nu (deg) or nubar (nd), already times 2 kappa
     double epst;       // 2 kappa epsbar (nd)
+    double del;        // MODE_SOLVE (nd): sqrt(epst^2 - nubar^2)
     double kfac;       // MODE_DIAG: coefficient of the hopping term
     int sgn;           // sign of the twist
     int t_bc;          // fermion time boundary factor
@@ -36,11 +38,12 @@ struct DslashArgs {
     double rho;        // MODE_DIAG, one flavour: adds i rho x to the final output (after g5out)
     int r0, rg;        // right-hand sides r0 .. r0 + rg - 1 of the nrhs per site (rg = 0: all)
     int spt;           // sites (slots) per thread: 1, or a grid-stride loop over spt of them
-    int ct;            // clov holds structured blocks (see load_ct)
-    double del;        // MODE_SOLVE (nd): sqrt(epst^2 - nubar^2)
 };
 
-struct DslashFused : DslashArgs {
+// (whole cache lines: the grid's sizes, which the runtime puts behind the
+// arguments, must not straddle one more: 376 instead of 384 bytes cost 0.2 us
+// a launch)
+struct alignas(64) DslashFused : DslashArgs {
     // of an iteration a solver has enqueued ahead: nothing runs if *stop < it
     const int *stop;
     int it;
