@@ -65,12 +65,20 @@ def kernel_bytes_per_site(kernel: str) -> float:
     return fixed + nrhs * spin
 
 
-def launch_bytes_per_site(kernel: str) -> float:
+def structured_bytes_per_site(kernel: str) -> float:
     """Bytes per output site of a one-flavour, one-right-hand-side launch on
     structured site blocks: 56 reals of A in either half instead of the 144 of
     the inverse (K1) and the 72 of the general block (K2)."""
     b = {"f64": 8, "f32": 4, "f16": 2}[kernel.split("_")[1]]
     return kernel_bytes_per_site(kernel) - (88 if kernel.startswith("K1") else 16) * b
+
+
+def launch_bytes_per_site(kernel: str, solver: bool = False) -> float:
+    """Bytes per output site that a one-flavour, one-right-hand-side launch
+    moves: structured blocks except in FP32's K1 (the stored inverse) and in FP16
+    outside a solver."""
+    stored = kernel.startswith("K1_f32") or ("_f16" in kernel and not solver)
+    return kernel_bytes_per_site(kernel) if stored else structured_bytes_per_site(kernel)
 
 
 def _stats(path):
@@ -136,7 +144,7 @@ def summarize(d: str, vh: int) -> str:
         if kname not in st:
             continue
         calls, avg = st[kname]
-        alg = (launch_bytes_per_site if ", true, tmx::DslashArgs>" in kname else kernel_bytes_per_site)(lab) * vh
+        alg = (structured_bytes_per_site if ", true, tmx::DslashArgs>" in kname else kernel_bytes_per_site)(lab) * vh
         fe = f[kname] * 1024 * sf
         wr = w[kname] * 1024 * sw
         rd = alg - (24 * {"f64": 8, "f32": 4, "f16": 2}[lab[3:]] + (4 if "f16" in lab else 0)) * vh
@@ -180,6 +188,7 @@ def kernel_table(stats_csv: str, title: str, command: str) -> str:
              f"{'calls':>6s} {'avg_us':>10s} {'total_ms':>10s} {'%':>6s}  kernel"]
     for name, calls, avg, tot, pct in rows:
         short = name.replace("void ", "").replace("(anonymous namespace)::", "").split("(")[0]
+        short = short.replace("tmx::Dslash", "Dslash")
         lines.append(f"{calls:6d} {avg / 1e3:10.1f} {tot / 1e6:10.2f} {pct:6.2f}  {short}")
     return "\n".join(lines) + "\n"
 
@@ -299,7 +308,7 @@ def sq_table(dirs) -> str:
         "# wait = SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES, valu = SQ_ACTIVE_INST_VALU / SQ_WAVE_CYCLES (per wave, summed",
         "#   over the dispatches of a kernel); insts per wave = SQ_INSTS_* / SQ_WAVES",
         "",
-        f"{'mode':8s} {'kernel':44s} {'disp':>4s} {'waves/disp':>10s} {'wait':>5s} {'valu':>5s} "
+        f"{'mode':8s} {'kernel':52s} {'disp':>4s} {'waves/disp':>10s} {'wait':>5s} {'valu':>5s} "
         f"{'valu/wave':>9s} {'vmem_rd/wave':>12s}",
     ]
     for item in dirs:
@@ -311,7 +320,8 @@ def sq_table(dirs) -> str:
             disp[r["Kernel_Name"]].add(r.get("Dispatch_Id", ""))
         for name in sorted(agg):
             short = name.replace("void ", "").replace("(anonymous namespace)::", "").split("(")[0]
-            if not any(t in short for t in ("dslash_kernel", "nn_", "force_kernel", "insertion_kernel", "loop_kernel",
+            short = short.replace("tmx::Dslash", "Dslash")
+            if not any(t in short for t in ("dslash_kernel", "dslash_pair_kernel", "nn_", "force_kernel", "insertion_kernel", "loop_kernel",
                                             "link_kernel")):
                 continue
             if "build" in short or "links" in short:
@@ -319,7 +329,7 @@ def sq_table(dirs) -> str:
             v, n = agg[name], max(len(disp[name]), 1)
             wc = max(v["SQ_WAVE_CYCLES"], 1.0)
             nw = max(v["SQ_WAVES"], 1.0)
-            lines.append(f"{label:8s} {short[:44]:44s} {n:4d} {nw / n:10.0f} {v['SQ_WAIT_INST_ANY'] / wc:5.2f} "
+            lines.append(f"{label:8s} {short[:52]:52s} {n:4d} {nw / n:10.0f} {v['SQ_WAIT_INST_ANY'] / wc:5.2f} "
                          f"{v['SQ_ACTIVE_INST_VALU'] / wc:5.2f} {v['SQ_INSTS_VALU'] / nw:9.0f} "
                          f"{v['SQ_INSTS_VMEM_RD'] / nw:12.0f}")
     return "\n".join(lines) + "\n"

@@ -507,8 +507,9 @@ __device__ __forceinline__ void dslash_slot(const A &a, int s, long rhs)
 // below about three waves per SIMD nothing else hides that.  Here wave w of a
 // workgroup takes both hops of direction w for the same 64 slots and leaves
 // the transported half spinors in LDS; after one barrier waves 0 and 1 sum
-// them in the order of the plain form (the results are the same bit for bit)
-// and finish one chirality each.  Site blocks and the other per-site operands
+// them in the order of the plain form (the two forms differ by the rounding of
+// products that the compiler fuses into sums in one of them) and finish one
+// chirality each.  Site blocks and the other per-site operands
 // are requested before the barrier.
 template <int P, typename R> struct SplitShared {
     cx<R> k[8][6][64];    // hop, component of the half spinor, slot
