@@ -237,8 +237,9 @@ int tmx_apply_mhat(tmx_ctx *ctx, void *out, const void *in, int op, int prec, in
  * precision of the one-flavour operator, and in FP32 / FP16 of the
  * two-flavour one), else TMX_EINVAL; the links, clover and site-block
  * inverses of this precision and sector must already be resident (any
- * tmx_apply_mhat or solve in them makes room for them), else TMX_ENOTLOADED.  Every call on
- * one GPU shares that scratch, which keeps the last call's contents
+ * tmx_apply_mhat or solve in them makes room for them), else TMX_ENOTLOADED.
+ * A captured call that finds them out of date records their build into its
+ * graph; later calls build their own.  Every call on one GPU shares that scratch, which keeps the last call's contents
  * (nothing in it needs clearing: each call overwrites what it reads): calls
  * that overlap on one GPU -- other streams, other contexts, other threads --
  * race and must be serialised by the caller. */

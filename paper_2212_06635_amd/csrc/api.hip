@@ -220,6 +220,15 @@ static size_t link_bytes(int prec, long Vh)
     return 8 * (size_t)Vh * (prec == F64 ? 96 : (prec == F32 ? 48 : 24));
 }
 
+// Whether what was just launched is there for later calls.  A build recorded by
+// a stream capture runs when the graph does: later calls build their own.
+static bool built(const tmx_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st == hipStreamCaptureStatusNone;
+}
+
 static int ensure_links(tmx_ctx *c, int prec)
 {
     if (!c->gauge_loaded) return set_err(c, TMX_ENOTLOADED, "no gauge field loaded");
@@ -231,7 +240,7 @@ static int ensure_links(tmx_ctx *c, int prec)
     int r = hip_err(c, launch_convert_links((const double *)c->links[F64], c->links[prec], prec, c->g, c->stream),
                     "convert links");
     if (r) return r;
-    c->links_ok[prec] = true;
+    c->links_ok[prec] = built(c);
     return TMX_OK;
 }
 
@@ -264,7 +273,7 @@ static int ensure_clover(tmx_ctx *c, int slot)
         r = hip_err(c, launch_clover_build((const double *)c->links[F64], cl, c->g, c->par.kappa, c->par.csw, c->stream),
                     "clover build");
         if (r) return r;
-        c->clov_ok[F64] = true;
+        c->clov_ok[F64] = built(c);
         c->clov_kappa = c->par.kappa;
         c->clov_csw = c->par.csw;
         c->clov_ok[F32] = c->clov_ok[F16] = c->clov_ok[F16A] = false;
@@ -282,7 +291,7 @@ static int ensure_clover(tmx_ctx *c, int slot)
                                               : launch_convert_seq(src, c->clov[slot], prec, 144, c->Vh, c->stream),
                     "convert clover");
         if (r) return r;
-        c->clov_ok[slot] = true;
+        c->clov_ok[slot] = built(c);
     }
     return TMX_OK;
 }
@@ -352,7 +361,7 @@ static int ensure_inv(tmx_ctx *c, int prec)
         r = hip_err(c, launch_clover_inv((const double *)c->clov[F64], clover_ct(c, F64), (double *)c->inv[F64], c->g, nu, c->stream),
                     "clover inverse");
         if (r) return r;
-        c->inv_ok[F64] = true;
+        c->inv_ok[F64] = built(c);
         c->inv_nu = nu;
         c->inv_ok[F32] = c->inv_ok[F16] = false;
     }
@@ -360,7 +369,7 @@ static int ensure_inv(tmx_ctx *c, int prec)
         r = hip_err(c, launch_convert_seq((const double *)c->inv[F64], c->inv[prec], prec, 144, c->Vh, c->stream),
                     "convert inverse");
         if (r) return r;
-        c->inv_ok[prec] = true;
+        c->inv_ok[prec] = built(c);
     }
     return TMX_OK;
 }
@@ -378,7 +387,7 @@ static int ensure_invnd(tmx_ctx *c, int prec)
                                             c->g, nb, ep, c->stream),
                     "nd clover inverse");
         if (r) return r;
-        c->invnd_ok[F64] = true;
+        c->invnd_ok[F64] = built(c);
         c->invnd_c = cc;
         c->invnd_ok[F32] = c->invnd_ok[F16] = false;
     }
@@ -386,7 +395,7 @@ static int ensure_invnd(tmx_ctx *c, int prec)
         r = hip_err(c, launch_convert_seq((const double *)c->invnd[F64], c->invnd[prec], prec, 72, c->Vh, c->stream),
                     "convert nd inverse");
         if (r) return r;
-        c->invnd_ok[prec] = true;
+        c->invnd_ok[prec] = built(c);
     }
     return TMX_OK;
 }
