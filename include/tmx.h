@@ -239,10 +239,11 @@ int tmx_apply_mhat(tmx_ctx *ctx, void *out, const void *in, int op, int prec, in
  * inverses of this precision and sector must already be resident (any
  * tmx_apply_mhat or solve in them makes room for them), else TMX_ENOTLOADED.
  * A captured call that finds them out of date records their build into its
- * graph; later calls build their own.  Every call on one GPU shares that scratch, which keeps the last call's contents
- * (nothing in it needs clearing: each call overwrites what it reads): calls
- * that overlap on one GPU -- other streams, other contexts, other threads --
- * race and must be serialised by the caller. */
+ * graph; later calls build their own.  Every call on one GPU shares that
+ * scratch, which keeps the last call's contents (nothing in it needs clearing:
+ * each call overwrites what it reads): calls that overlap on one GPU -- other
+ * streams, other contexts, other threads -- race and must be serialised by the
+ * caller. */
 int tmx_apply_mhat_noalloc(tmx_ctx *ctx, void *out, const void *in, int op, int prec, int dagger, int nrhs);
 /* out = N in = Mhat^dagger Mhat in, the Hermitian positive operator whose
  * solves the monomials need (Section 2: Q-hat^+ Q-hat^- = Mhat(-)^dagger
